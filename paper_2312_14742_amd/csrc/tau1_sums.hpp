@@ -1,0 +1,268 @@
+// tau1_sums.hpp -- equilibria and moment sums shared by every 3-D step kernel
+// (z-march tiles, chunk kernel, row kernel), so that all of them form each
+// destination sum with the same roundings.
+//
+// The directions of a lattice fall into nine groups by (c_y, c_z); a group
+// holds at most the directions c_x = 0, +1, -1.  What a group sends to a node
+// is needed in two forms only: its density sum
+//   t = f_0(x) * W0 + WX * (f_+(x - 1) + f_-(x + 1)),
+// which is also its momentum along y (times c_y) and z (times c_z), and the
+// difference e = WX * (f_+(x - 1) - f_-(x + 1)), its momentum along x.  All
+// weights are multiples of one unit (1/72, 1/36, 1/216 for D3Q15, D3Q19,
+// D3Q27), so sums run over small integers and the unit is applied once per
+// node.  Per node and step this takes 34 additions on D3Q19 and 53 on D3Q27
+// where a sum per direction and component takes 49 and 81.
+//
+// A plane's sums are kept by the source plane they came from:
+//   T  from plane z - 1 (c_z = +1), C from plane z, M from plane z + 1:
+//   rho - 1 = unit * (T + M) + unit * C,   j_z = T - M,
+// so j_z costs one subtraction and a fresh plane needs no clearing.  Wall
+// returns with z-momentum r_z go into T, and r_z is taken off C again.
+//
+// The equilibria of a source are evaluated level by level: f along (c_x, c_y,
+// c_z) is a quadratic in each velocity component, so the value and slope at
+// (c_y, 0) give those at (c_y, c_z), and those give the two directions c_x =
+// +-1 with one shared term (38 operations for the 18 directions of D3Q19
+// against 46 one by one).
+//
+// Measured against a sum per direction and component (MI355X, 1000 steps with
+// readback): D3Q19 FP16 256^3 181 -> 145 ms, D3Q27 FP32 256^3 (500 steps) 138
+// -> 131 ms, a batch of 12 samples 414 -> 398 ms; D3Q19 FP32 512^3 and the
+// chunk kernel, bound by their memory accesses, 1-2 %.
+#pragma once
+
+#include "tau1_args.hpp"
+
+// Multiply-adds fuse only where one expression writes a * b + c (and at the
+// explicit fma calls), never across statements: every kernel, tile and load
+// schedule then forms each sum with the same roundings, so results do not
+// depend on the kernel or tile chosen.
+#pragma clang fp contract(on)
+
+namespace tau1 {
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Per-source quantities: the equilibrium of Eq. (3) minus its weight in a
+// direction with cu = c.v is w * (A + cu * (R3 + R45 * cu)) with
+// A = drho - 1.5 rho v.v, R3 = 3 rho, R45 = 1.5 R3 (= 4.5 rho), rho = 1 + drho.
+// R45 is always formed from R3, so a source shared as (A, R3, v) gives the
+// same bits wherever it is evaluated.
+template <typename T>
+struct SrcT {
+    T a, r3, r45, vx, vy, vz;
+};
+using Src = SrcT<float>;
+
+template <typename T>
+__device__ __forceinline__ SrcT<T> make_src(T d, T vx, T vy, T vz) {
+    SrcT<T> s;
+    const T rho = (T)1 + d;
+    const T vv = vx * vx + vy * vy + vz * vz;
+    s.a = fma_t((T)-1.5 * rho, vv, d);
+    s.r3 = (T)3 * rho;
+    s.r45 = (T)1.5 * s.r3;
+    s.vx = vx;
+    s.vy = vy;
+    s.vz = vz;
+    return s;
+}
+
+// Weight of a direction with n nonzero components, in units (0: the lattice
+// has no such direction), and the unit.
+template <int Q>
+constexpr int weight_units(int n) {
+    using L = Lattice<Q>;
+    const double w = n == 0 ? L::w_rest : n == 1 ? L::w_face : n == 2 ? L::w_edge : L::w_corner;
+    return (int)(w * L::units + 0.5);
+}
+template <int Q, typename T>
+constexpr T weight_unit() { return (T)(1.0 / Lattice<Q>::units); }
+
+// One group of directions (c_y, c_z): whether it holds c_x = 0 and c_x = +-1,
+// and their weights.  t is formed as R f_0 + (f_+ + f_-) and added with
+// weight WG.
+template <int Q, int CY, int CZ>
+struct Group {
+    static constexpr int n = (CY != 0) + (CZ != 0);
+    static constexpr int w0 = weight_units<Q>(n), wx = weight_units<Q>(n + 1);
+    static constexpr bool has0 = w0 > 0, hasx = wx > 0;
+    static constexpr int r = hasx ? w0 / wx : 1;
+    static constexpr int wg = hasx ? wx : w0;
+    static_assert(!(has0 && hasx) || w0 % wx == 0, "whole weight ratio");
+};
+
+// acc + W * v.
+template <int W, typename T>
+__device__ __forceinline__ T add_w(T acc, T v) {
+    if constexpr (W == 1) return acc + v;
+    else if constexpr (W == -1) return acc - v;
+    else return fma_t((T)W, v, acc);
+}
+// W * v.
+template <int W, typename T>
+__device__ __forceinline__ T mul_w(T v) {
+    if constexpr (W == 1) return v;
+    else return (T)W * v;
+}
+
+// f and slope of a source along (0, CY, 0): f = a + cu (r3 + r45 cu) at cu =
+// CY vy, slope g = r3 + 2 r45 cu.
+template <int CY, typename T>
+__device__ __forceinline__ void level_y(const SrcT<T>& s, T& f, T& g) {
+    if constexpr (CY == 0) {
+        f = s.a;
+        g = s.r3;
+    } else {
+        const T cu = CY > 0 ? s.vy : -s.vy;
+        const T h = fma_t(s.r45, cu, s.r3);
+        f = fma_t(h, cu, s.a);
+        g = fma_t(s.r45, cu, h);
+    }
+}
+
+// ... along (0, CY, CZ), from those along (0, CY, 0).
+template <int CZ, typename T>
+__device__ __forceinline__ void level_z(const SrcT<T>& s, T& f, T& g) {
+    if constexpr (CZ != 0) {
+        const T tz = s.r45 * s.vz;
+        const T q = fma_t(tz, s.vz, f);
+        f = fma_t(CZ > 0 ? g : -g, s.vz, q);
+        g = fma_t(CZ > 0 ? (T)2 : (T)-2, tz, g);
+    }
+}
+
+// f along (+1, CY, CZ) and (-1, CY, CZ).
+template <typename T>
+__device__ __forceinline__ void level_x(const SrcT<T>& s, T f, T g, T& fp, T& fm) {
+    const T tx = s.r45 * s.vx;
+    const T q = fma_t(tx, s.vx, f);
+    fp = fma_t(g, s.vx, q);
+    fm = fma_t(-g, s.vx, q);
+}
+
+// Partial sums of one node of a destination plane (roles in the file header).
+// t: T; s: C; x, y: momentum along x and y.
+//
+// Adds group (CY, CZ)'s density sum t and x-difference e (weights WG, WX) to
+// the plane it goes to.  The first group a plane receives sets its sums: T at
+// (0, +1), y at (+1, +1), x at the first group with c_x, C at (0, 0), and M
+// (one plane's, of the current step only) at (0, -1).
+template <int Q, int CY, int CZ, typename T>
+__device__ __forceinline__ void add_group(T t, T e, T& pt, T& ps, T& px, T& py, T& m) {
+    using G = Group<Q, CY, CZ>;
+    if constexpr (CZ > 0) {
+        if constexpr (CY == 0) pt = mul_w<G::wg>(t);
+        else pt = add_w<G::wg>(pt, t);
+        if constexpr (CY > 0) py = mul_w<G::wg>(t);
+    } else if constexpr (CZ == 0) {
+        if constexpr (CY == 0) ps = mul_w<G::wg>(t);
+        else ps = add_w<G::wg>(ps, t);
+        if constexpr (CY > 0) py = add_w<G::wg>(py, t);
+    } else {
+        if constexpr (CY == 0) m = mul_w<G::wg>(t);
+        else m = add_w<G::wg>(m, t);
+        if constexpr (CY > 0) py = add_w<G::wg>(py, t);
+    }
+    if constexpr (CY < 0) py = add_w<-G::wg>(py, t);
+    if constexpr (G::hasx) {
+        constexpr bool first = CZ > 0 && (CY == 0 || (CY > 0 && !Group<Q, 0, 1>::hasx));
+        if constexpr (first) px = mul_w<G::wx>(e);
+        else px = add_w<G::wx>(px, e);
+    }
+}
+
+// A group's t from f_0 and the two arriving neighbours' values.
+template <int Q, int CY, int CZ, typename T>
+__device__ __forceinline__ T group_sum(T f0, T fp, T fm) {
+    using G = Group<Q, CY, CZ>;
+    if constexpr (!G::hasx) return f0;
+    else if constexpr (!G::has0) return fp + fm;
+    else return fma_t((T)G::r, f0, fp + fm);
+}
+
+// Index of direction (x, y, z) in the lattice's order, or 0.
+template <int Q>
+constexpr int dir_index(int x, int y, int z) {
+    for (int k = 1; k < Q; ++k)
+        if (Lattice<Q>::c[k].x == x && Lattice<Q>::c[k].y == y && Lattice<Q>::c[k].z == z) return k;
+    return 0;
+}
+
+// Halfway bounce-back (Eq. 11) at one node: every direction k whose neighbour
+// x + c_k is solid returns the node's own equilibrium in k along -c_k.
+// pick(k, u) is u where that neighbour is solid, else zero (the kernels keep
+// the solid links in different forms).  r: what a kernel adds to C (density
+// less z-momentum), x, y and T (z-momentum), in units.
+template <int Q, int CX, int CY, int CZ, typename T, typename Pick>
+__device__ __forceinline__ void wall_dir(T f, const Pick& pick, T (&r)[4]) {
+    constexpr int w = weight_units<Q>((CX != 0) + (CY != 0) + (CZ != 0));
+    const T u = pick(std::integral_constant<int, dir_index<Q>(CX, CY, CZ)>{}, f);
+    r[0] = add_w<w>(r[0], u);
+    if constexpr (CX != 0) r[1] = add_w<-CX * w>(r[1], u);
+    if constexpr (CY != 0) r[2] = add_w<-CY * w>(r[2], u);
+    if constexpr (CZ != 0) r[3] = add_w<-CZ * w>(r[3], u);
+}
+
+template <int Q, int CY, int CZ, typename T, typename Pick>
+__device__ __forceinline__ void wall_group(const SrcT<T>& s, T f, T g, const Pick& pick, T (&r)[4]) {
+    using G = Group<Q, CY, CZ>;
+    level_z<CZ>(s, f, g);
+    if constexpr (G::has0 && (CY != 0 || CZ != 0)) wall_dir<Q, 0, CY, CZ>(f, pick, r);
+    if constexpr (G::hasx) {
+        T fp, fm;
+        level_x(s, f, g, fp, fm);
+        wall_dir<Q, 1, CY, CZ>(fp, pick, r);
+        wall_dir<Q, -1, CY, CZ>(fm, pick, r);
+    }
+}
+
+template <int Q, int CY, typename T, typename Pick>
+__device__ __forceinline__ void wall_row(const SrcT<T>& s, const Pick& pick, T (&r)[4]) {
+    T f, g;
+    level_y<CY>(s, f, g);
+    wall_group<Q, CY, 0>(s, f, g, pick, r);
+    wall_group<Q, CY, 1>(s, f, g, pick, r);
+    wall_group<Q, CY, -1>(s, f, g, pick, r);
+}
+
+template <int Q, typename T, typename Pick>
+__device__ __forceinline__ void wall_sums(const SrcT<T>& s, const Pick& pick, T (&r)[4]) {
+    r[0] = r[1] = r[2] = r[3] = (T)0;
+    wall_row<Q, 0>(s, pick, r);
+    wall_row<Q, 1>(s, pick, r);
+    wall_row<Q, -1>(s, pick, r);
+    r[0] -= r[3];
+}
+
+// The link selection of a kernel that keeps one all-ones / zero word per link.
+template <typename Link>
+struct PickMask {
+    const Link& link;
+    template <typename K>
+    __device__ __forceinline__ float operator()(K, float u) const {
+        return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, u) & link(K::value));
+    }
+};
+
+// New state of one node from its sums (file header): v = j / rho + g with one
+// reciprocal; FP32 uses the hardware's, FP64 divides.  unit * C is rounded
+// before the sum's last addition, at two thirds of its size or less, so that
+// the unit costs less rounding than one more full-size addition.
+__device__ __forceinline__ float recip_t(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double recip_t(double x) { return 1.0 / x; }
+
+template <int Q, typename T>
+__device__ __forceinline__ void finish_node(T t, T c, T m, T jx, T jy, T gx, T gy, T gz, T& d,
+                                            T& vx, T& vy, T& vz) {
+    constexpr T unit = weight_unit<Q, T>();
+    const T uc = unit * c, tm = t + m;
+    d = fma_t(unit, tm, uc);
+    const T r = recip_t((T)1 + d) * unit;
+    vx = fma_t(jx, r, gx);
+    vy = fma_t(jy, r, gy);
+    vz = fma_t(t - m, r, gz);
+}
+
+}  // namespace tau1
