@@ -104,7 +104,8 @@ typedef struct {
     void *workspace;        /* borrowed device memory, 256-byte aligned         */
     size_t workspace_bytes;
     int32_t kernel;         /* step kernel: -1 = automatic (tuned or default),
-                               0 = per-node gather, 1 = z-march tiles        */
+                               0 = row kernel (one node per lane, rows of any
+                               length, every precision), 1 = z-march tiles  */
     int32_t tile;           /* z-march tile shape, -1 = automatic; 0-15 =
                                z-segment of 16/32/64/128 planes (tile % 4) x
                                load schedule (tile / 4: 0 just in time,
@@ -157,7 +158,7 @@ typedef struct {
 /* Static facts about a created context (host copy). */
 typedef struct {
     int32_t lattice, precision, n_samples;
-    int32_t kernel;          /* step kernel in use: 0 per-node gather,
+    int32_t kernel;          /* step kernel in use: 0 row kernel,
                                 1 z-march tiles, 2 D2Q9                     */
     int32_t tile;            /* tile in use (z-march tiles and the chunk
                                 tile); in a batch, that of the lane layout
@@ -174,7 +175,7 @@ typedef struct {
     int64_t work_items;      /* work items per step: z-march row groups x
                                 z-segments holding a fluid node, or waves of
                                 64 stored chunks for the chunk tile; 0 for
-                                the gather kernel                           */
+                                the row kernel                              */
     int32_t launches_per_step; /* kernel launches one step takes (one per
                                 z-march lane layout, or one for all the
                                 one-chunk rows with batch_graph 3)          */

@@ -4,7 +4,8 @@ Run ``python -m paper_2312_14742_amd.build`` or call :func:`build`.  hipcc
 cross-compiles for gfx950 without a GPU present.  The z-march kernels of each
 (lattice, precision) pair are two translation units of their own (the
 per-layout kernels, and the one-launch kernels of a batch's one-row layouts),
-compiled in parallel, then linked with the host API into one shared library.
+and the row kernels of each precision are one; all are compiled in parallel,
+then linked with the host API into one shared library.
 """
 from __future__ import annotations
 
@@ -47,6 +48,9 @@ def build(verbose: bool = False, extra: list[str] | None = None, jobs: int | Non
     extra = extra or []
     jobs = jobs or min(8, os.cpu_count() or 1)
     units = [(os.path.join(CSRC, "tau1_api.hip"), os.path.join(OBJDIR, "tau1_api.o"), [])]
+    for p in range(4):
+        units.append((os.path.join(CSRC, "tau1_lines.hip"),
+                      os.path.join(OBJDIR, f"tau1_ln_{p}.o"), [f"-DTAU1_P={p}"]))
     for q, p in PAIRS:
         units.append((os.path.join(CSRC, "tau1_zmarch_inst.hip"),
                       os.path.join(OBJDIR, f"tau1_zm_{q}_{p}.o"),

@@ -17,6 +17,7 @@
 #include "tau1_device.hpp"
 #include "tau1_kernels.hpp"
 #include "tau1_zmarch.hpp"
+#include "tau1_lines.hpp"
 #include "tau1_service.hpp"
 
 using namespace tau1;
@@ -212,12 +213,15 @@ Plan make_plan(const tau1_desc* d, bool tables) {
         sd.n = in.nx * in.ny * in.nz;
         sd.words = (int32_t)((in.nx + 31) / 32);
         sd.stride = (int64_t)(align_up((size_t)sd.n * sz, kAlign) / sz);
-        sd.block0 = blocks;
-        blocks += (sd.n + kGatherBlock - 1) / kGatherBlock;
         zmarch_tiling(sd);
-        if (d->lattice == 9) sd.variant = -1;  // the D2Q9 kernel only
+        if (d->lattice == 9) {
+            sd.variant = -1;  // the D2Q9 kernel only
+            sd.block0 = blocks;
+            blocks += (sd.n + kNodeBlock - 1) / kNodeBlock;
+        }
         maxn = std::max<int64_t>(maxn, sd.n);
     }
+    if (d->lattice != 9) blocks = lines_tiling(p.s.data(), d->n_samples, d->precision);
     // packed layout: by default for the z-march precisions (FP32 and the
     // 16-bit storage modes) unless a dense-layout tile is asked for;
     // one-row-per-wave lane layouts only, and only where the z-march kernel
@@ -412,27 +416,6 @@ tau1_status fail_hip(tau1_ctx* ctx, hipError_t e) {
 }
 
 // --- kernel dispatch -------------------------------------------------------
-template <int Q, int P>
-void* gather_fn() { return reinterpret_cast<void*>(&k_gather<Q, P>); }
-
-void* pick_gather(int q, int p) {
-    switch (q * 10 + p) {
-        case 150: return gather_fn<15, kF64>();
-        case 151: return gather_fn<15, kF32>();
-        case 152: return gather_fn<15, kF16>();
-        case 153: return gather_fn<15, kBF16>();
-        case 190: return gather_fn<19, kF64>();
-        case 191: return gather_fn<19, kF32>();
-        case 192: return gather_fn<19, kF16>();
-        case 193: return gather_fn<19, kBF16>();
-        case 270: return gather_fn<27, kF64>();
-        case 271: return gather_fn<27, kF32>();
-        case 272: return gather_fn<27, kF16>();
-        case 273: return gather_fn<27, kBF16>();
-    }
-    return nullptr;
-}
-
 // Launch geometry of one step for the chosen kernel.
 struct Launch {
     void* fn;
@@ -461,8 +444,8 @@ int group_mode(const tau1_ctx::ZGroup& g) {
     return tile_mode(zt) == 3 && !g.packed ? 1 : tile_mode(zt);
 }
 
-// Launch geometry of one step kernel: z-march group g (kernel 1), the
-// per-node gather over every sample (kernel 0) or the D2Q9 kernel (2).
+// Launch geometry of one step kernel: z-march group g (kernel 1), the row
+// kernel over every sample (kernel 0) or the D2Q9 kernel (2).
 Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
     Launch l{};
     if (kernel == 1) tile = ctx->zgroups[g].tile;
@@ -485,10 +468,15 @@ Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
         l.block = dim3(zmarch_threads(tile));
         l.grid = dim3((unsigned)zmarch_grid(grp.args[0].ntiles, tile));
         l.shmem = 0;
-    } else {
-        l.fn = kernel == 2 ? pick_d2q9(ctx->precision) : pick_gather(ctx->lattice, ctx->precision);
-        l.block = dim3(kGatherBlock);
+    } else if (kernel == 2) {
+        l.fn = pick_d2q9(ctx->precision);
+        l.block = dim3(kNodeBlock);
         l.grid = dim3((unsigned)ctx->plan.total_blocks);
+        l.shmem = 0;
+    } else {
+        l.fn = pick_lines(ctx->lattice, ctx->precision);
+        l.block = dim3(kLnThreads);
+        l.grid = dim3((unsigned)((ctx->plan.total_blocks + 7) / 8 * 8));  // whole XCD rounds
         l.shmem = 0;
     }
     return l;
@@ -1054,6 +1042,7 @@ tau1_status tau1_create(const tau1_desc* desc, tau1_ctx** out) {
         a.tiles = reinterpret_cast<const int32_t*>(ctx->base + ctx->plan.tiles_off);
         a.nsamples = ctx->nsamples;
         a.ntiles = (int32_t)ctx->plan.ntiles;
+        a.lblocks = (int32_t)ctx->plan.total_blocks;
         a.parity = p;
         for (int d = 0; d < 3; ++d) {
             a.gh[d] = 0.5 * desc->g[d];
@@ -1237,7 +1226,7 @@ tau1_status tau1_autotune(tau1_ctx* ctx, int32_t trial_steps) {
     tau1_status st = check_usable(ctx);
     if (st != TAU1_OK) return st;
     if (trial_steps < 1) return TAU1_E_INVALID;
-    if (!zmarch_eligible(ctx)) return TAU1_OK;  // only the gather kernel applies
+    if (!zmarch_eligible(ctx)) return TAU1_OK;  // only the row kernel applies
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));

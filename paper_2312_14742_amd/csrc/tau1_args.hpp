@@ -16,7 +16,7 @@ struct StepArgs {
     int32_t nsamples;
     int32_t parity;             // buffer read this step; the other is written
     int32_t ntiles;             // z-march work items
-    int32_t pad;
+    int32_t lblocks;            // row kernel: workgroups holding work
     double gh[3];               // g / 2 (FP64)
     float ghf[3];               // g / 2 (FP32)
     float scale_rho, inv_scale_rho, scale_u, inv_scale_u;  // F16 storage

@@ -180,6 +180,9 @@ struct SampleDev {
     int32_t variant;      // z-march lane layout (-1: not supported)
     int32_t tiles_y;      // z-march row groups
     int32_t pk;           // packed layout: nodes per chunk; 0 = dense layout
+    // row kernel (k_lines): windows per row, nodes per window, lanes taken by
+    // the neighbours at either end of a window (0 or 1), planes per z-segment
+    int32_t ln_windows, ln_nodes, ln_halo, ln_lz;
 };
 
 // Solid bit of node (x, y, z).

@@ -1,4 +1,4 @@
-// tau1_kernels.hpp -- per-node gather step kernel and the service kernels
+// tau1_kernels.hpp -- D2Q9 step kernel and the service kernels
 // (geometry encode, state upload/readback, FP64 reductions, copy probe).
 #pragma once
 
@@ -16,88 +16,14 @@ __device__ __forceinline__ int sample_of_block(const SampleDev* s, int n, int64_
     return lo;
 }
 
-constexpr int kGatherBlock = 256;
+constexpr int kNodeBlock = 256;
 
 // ---------------------------------------------------------------------------
-// Per-node gather step (pull form).  One thread per node; the node reads the
-// pre-step (drho, v) of each source x - c_k (periodic wrap, then the solid
-// test), forms the equilibrium of Eq. (3) minus its weight and accumulates
-// density and momentum in direction order; a solid source is replaced by the
-// node's own state with the opposite direction (halfway bounce-back, Eq. (11)).
-// One reciprocal per node (division-saving algorithm).  Contraction into FMA
-// is disabled so the FP64 instance reproduces plain IEEE evaluation.
-// ---------------------------------------------------------------------------
-template <int Q, int P>
-__global__ __launch_bounds__(kGatherBlock) void k_gather(StepArgs a) {
-#pragma clang fp contract(off)
-    using St = Storage<P>;
-    using S = typename St::S;
-    using T = typename St::T;
-    using L = Lattice<Q>;
-    const int s = sample_of_block(a.samples, a.nsamples, blockIdx.x);
-    const SampleDev& sd = a.samples[s];
-    const int64_t i = (int64_t)(blockIdx.x - sd.block0) * kGatherBlock + threadIdx.x;
-    if (i >= sd.n) return;
-    const int nx = sd.nx, ny = sd.ny, nz = sd.nz;
-    const int x = (int)(i % nx);
-    const int y = (int)((i / nx) % ny);
-    const int z = (int)(i / ((int64_t)nx * ny));
-    const uint32_t* mask = reinterpret_cast<const uint32_t*>(a.base + sd.mask);
-    if (solid_bit(mask, sd.words, ny, x, y, z)) return;
-
-    const S* pre = reinterpret_cast<const S*>(a.base + sd.state[a.parity]);
-    S* post = reinterpret_cast<S*>(a.base + sd.state[a.parity ^ 1]);
-    const int64_t st = sd.stride;
-    const T isr = inv_scale_rho<P>(a), isu = inv_scale_u<P>(a);
-    const T d0 = St::load(pre, i, isr);
-    const T v0x = St::load(pre + st, i, isu);
-    const T v0y = St::load(pre + 2 * st, i, isu);
-    const T v0z = St::load(pre + 3 * st, i, isu);
-
-    T d = 0, jx = 0, jy = 0, jz = 0;
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        const int cx = L::c[k].x, cy = L::c[k].y, cz = L::c[k].z;
-        int sx = x - cx, sy = y - cy, sz = z - cz;
-        sx += sx < 0 ? nx : 0; sx -= sx >= nx ? nx : 0;
-        sy += sy < 0 ? ny : 0; sy -= sy >= ny ? ny : 0;
-        sz += sz < 0 ? nz : 0; sz -= sz >= nz ? nz : 0;
-        T ds, vx, vy, vz, ex, ey, ez;
-        if (!solid_bit(mask, sd.words, ny, sx, sy, sz)) {
-            const int64_t j = sx + (int64_t)nx * (sy + (int64_t)ny * sz);
-            ds = St::load(pre, j, isr);
-            vx = St::load(pre + st, j, isu);
-            vy = St::load(pre + 2 * st, j, isu);
-            vz = St::load(pre + 3 * st, j, isu);
-            ex = (T)cx; ey = (T)cy; ez = (T)cz;
-        } else {
-            ds = d0; vx = v0x; vy = v0y; vz = v0z;
-            ex = (T)-cx; ey = (T)-cy; ez = (T)-cz;
-        }
-        const T rho = (T)1 + ds;
-        const T cu = (ex * vx + ey * vy) + ez * vz;
-        const T vv = (vx * vx + vy * vy) + vz * vz;
-        const T p = ((T)3 * cu + ((T)4.5 * cu) * cu) - (T)1.5 * vv;
-        const T f = (T)weight<Q>(k) * (ds + rho * p);
-        d += f;
-        jx += (T)cx * f;
-        jy += (T)cy * f;
-        jz += (T)cz * f;
-    }
-    const T r = (T)1 / ((T)1 + d);
-    const T ghx = gh_of<T>(a, 0), ghy = gh_of<T>(a, 1), ghz = gh_of<T>(a, 2);
-    const T ux = jx * r + ghx, uy = jy * r + ghy, uz = jz * r + ghz;
-    const T sr = scale_rho<P>(a), su = scale_u<P>(a);
-    St::store(post, i, d, sr);
-    St::store(post + st, i, ux + ghx, su);
-    St::store(post + 2 * st, i, uy + ghy, su);
-    St::store(post + 3 * st, i, uz + ghz, su);
-}
-
-// ---------------------------------------------------------------------------
-// D2Q9 step of the validation workloads (nz = 1), one thread per node, pull
-// form as k_gather, with node types: a wall source (type 1) returns the node's
-// own equilibrium in the opposite direction (halfway bounce-back, Eq. (11));
+// D2Q9 step of the validation workloads (nz = 1), one thread per node, in pull
+// form: the node reads the pre-step (drho, v) of each source x - c_k (periodic
+// wrap, then the wall test), forms the equilibrium of Eq. (3) minus its weight
+// and adds density and momentum in direction order; a wall source (type 1)
+// returns the node's own equilibrium in the opposite direction (Eq. (11));
 // a moving wall (type 2) adds the wall's momentum to it,
 //   f_k(x) = f_opp(k)(x) + 6 w_k rho(x) (c_k . u_wall).
 // With a.xbc the fluid nodes of columns x = 0 and nx - 1 are constant-pressure
@@ -109,7 +35,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather(StepArgs a) {
 // FP64 reproduces the oracle's roundings (contraction off).
 // ---------------------------------------------------------------------------
 template <int P>
-__global__ __launch_bounds__(kGatherBlock) void k_d2q9(StepArgs a) {
+__global__ __launch_bounds__(kNodeBlock) void k_d2q9(StepArgs a) {
 #pragma clang fp contract(off)
     using St = Storage<P>;
     using S = typename St::S;
@@ -117,7 +43,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_d2q9(StepArgs a) {
     using L = Lattice<9>;
     const int s = sample_of_block(a.samples, a.nsamples, blockIdx.x);
     const SampleDev& sd = a.samples[s];
-    const int64_t i = (int64_t)(blockIdx.x - sd.block0) * kGatherBlock + threadIdx.x;
+    const int64_t i = (int64_t)(blockIdx.x - sd.block0) * kNodeBlock + threadIdx.x;
     if (i >= sd.n) return;
     const int nx = sd.nx, ny = sd.ny;
     const int x = (int)(i % nx);
