@@ -106,7 +106,9 @@ typedef struct {
     int32_t kernel;         /* step kernel: -1 = automatic (tuned or default),
                                0 = row kernel (one node per lane, rows of any
                                length, every precision), 1 = z-march tiles  */
-    int32_t tile;           /* z-march tile shape, -1 = automatic; 0-15 =
+    int32_t tile;           /* z-march tile shape, -1 = automatic (the layout's
+                               usual schedule, with z-segments as short as
+                               fills the card); 0-15 =
                                z-segment of 16/32/64/128 planes (tile % 4) x
                                load schedule (tile / 4: 0 just in time,
                                1 rows shared through LDS, 2 rolling prefetch,
@@ -161,7 +163,9 @@ typedef struct {
     int32_t kernel;          /* step kernel in use: 0 row kernel,
                                 1 z-march tiles, 2 D2Q9                     */
     int32_t tile;            /* tile in use (z-march tiles and the chunk
-                                tile); in a batch, that of the lane layout
+                                tile; after an automatic choice, whose
+                                z-segments may be shorter than the tile's,
+                                the nearest one); in a batch, that of the lane layout
                                 with the most fluid nodes (tau1_autotune
                                 gives each layout its own)                 */
     int32_t graph_chunk;
@@ -256,8 +260,9 @@ tau1_status tau1_permeability(tau1_ctx *ctx, int32_t sample,
 tau1_status tau1_permeability_noalloc(tau1_ctx *ctx, int32_t sample,
                                       int32_t axis, double *out);
 
-/* Times each eligible step-kernel shape for trial_steps steps (state is not
- * advanced: trials write only the spare buffer), keeps the fastest and, if
+/* Times each eligible step-kernel shape for trial_steps steps (all but those
+ * whose z-segments are far too long for the lattice; state is not advanced:
+ * trials write only the spare buffer), keeps the fastest and, if
  * the descriptor named a cache file, records it there.  In a batch each lane
  * layout is timed alone and gets its own tile; with batch_graph 3 the whole
  * step is then timed with those tiles and with each z-march tile for every

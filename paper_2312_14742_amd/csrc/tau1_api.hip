@@ -270,15 +270,12 @@ Plan make_plan(const tau1_desc* d, bool tables) {
         sh.ck = (d->tile == kChunkTile || 2 * sh.nch <= all) && sh.nch <= (int64_t)kRecIndex;
     }
     p.pack_refused = d->layout == 1 && !p.packed;
-    // work-list capacity: the longest z-march list (16-plane segments) or the
-    // chunk tile's list (one item per 64 stored chunks), whichever is longer
-    tiles = zmarch_max_items(p.s.data(), d->n_samples);
-    {
-        int64_t ck = 0;
-        for (const auto& sh : p.s)
-            if (sh.ck) ck += (sh.nch + 63) / 64;
-        tiles = std::max(tiles, ck);
-    }
+    // work-list capacity: per sample its longest z-march list or its chunk list
+    // (one item per 64 stored chunks), whichever is longer (a batch may run one
+    // lane layout at the one and another at the other)
+    const int lz_min = zmarch_min_lz(p.s.data(), d->n_samples);
+    for (const auto& sh : p.s)
+        tiles += std::max(zmarch_items(sh.dev, lz_min), sh.ck ? (sh.nch + 63) / 64 : 0);
     p.total_blocks = blocks;
     p.ntiles = tiles;
     p.tiles_off = off;
@@ -381,6 +378,8 @@ struct tau1_ctx {
     struct ZGroup {
         int variant;
         int tile;     // its tile (the autotuner picks one per lane layout)
+        int lz;       // planes per z-segment: the tile's, or fewer where the
+                      // choice was automatic
         bool packed;  // its samples use the packed layout
         bool chunks;  // ... and hold the chunk tile's list and records
         int rows_mode = -1;  // >= 0: several one-row layouts in one launch
@@ -440,8 +439,19 @@ void* pick_d2q9(int p) {
 // context runs the dense shared-row schedule), or -1 for the chunk kernel.
 int group_mode(const tau1_ctx::ZGroup& g) {
     if (g.tile == kChunkTile && g.chunks) return -1;
-    const int zt = tile_zmarch(g.tile);
-    return tile_mode(zt) == 3 && !g.packed ? 1 : tile_mode(zt);
+    const int mode = g.tile == kChunkTile ? 3 : tile_mode(g.tile);
+    return mode == 3 && !g.packed ? 1 : mode;
+}
+
+// Workgroups of group g's z-march kernel that a CU holds.
+int group_resident(const tau1_ctx* ctx, const tau1_ctx::ZGroup& g) {
+    int n = 0;
+    const void* fn = pick_zmarch(ctx->lattice, ctx->precision, g.variant, group_mode(g));
+    if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kZrThreads, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 2;
+    }
+    return std::clamp(n, 1, 8);
 }
 
 // Launch geometry of one step kernel: z-march group g (kernel 1), the row
@@ -459,14 +469,13 @@ Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
         const auto& grp = ctx->zgroups[g];
         l.fn = pick_zmarch_rows(ctx->lattice, ctx->precision, grp.rows_mode);
         l.block = dim3(kZrThreads);
-        l.grid = dim3((unsigned)zmarch_grid(grp.args[0].ntiles, tile));
+        l.grid = dim3((unsigned)zmarch_grid(grp.args[0].ntiles));
         l.shmem = 0;
     } else if (kernel == 1) {
         const auto& grp = ctx->zgroups[g];
-        tile = tile_zmarch(tile);
         l.fn = pick_zmarch(ctx->lattice, ctx->precision, grp.variant, group_mode(grp));
-        l.block = dim3(zmarch_threads(tile));
-        l.grid = dim3((unsigned)zmarch_grid(grp.args[0].ntiles, tile));
+        l.block = dim3(kZrThreads);
+        l.grid = dim3((unsigned)zmarch_grid(grp.args[0].ntiles));
         l.shmem = 0;
     } else if (kernel == 2) {
         l.fn = pick_d2q9(ctx->precision);
@@ -769,6 +778,18 @@ tau1_status export_sample_t(tau1_ctx* ctx, int s, double* drho, double* u, int* 
     return TAU1_OK;
 }
 
+// Whether z-march group g's segments put it at over twice the modelled time of
+// the best length (never for the shortest tile, so that one is always timed).
+bool far_from_best(const tau1_ctx* ctx, const tau1_ctx::ZGroup& g) {
+    if (tile_lz(g.tile) == kTileLZ[0]) return false;
+    const auto* s = ctx->plan.s.data();
+    const int n = ctx->nsamples, res = group_resident(ctx, g);
+    const bool blocks = zr_share(kVariants[g.variant].g, group_mode(g));
+    const int best = zmarch_segment(s, n, g.variant, blocks, res);
+    return zmarch_cost(s, n, g.variant, blocks, res, g.lz) >
+           2.0 * zmarch_cost(s, n, g.variant, blocks, res, best);
+}
+
 // Enqueues the two reduction kernels of one sample: block partials into
 // `partial` (kReduceBlocks x 4 doubles, every entry written), then the four
 // results into `res`.
@@ -806,7 +827,7 @@ tau1_status reduce_ws(tau1_ctx* ctx, int s, int axis, double out[4]) {
 }
 
 // Selects the tile of every lane layout (`tile`, or per_variant[v] where
-// that is given and not negative), rebuilds and uploads the work lists;
+// that is given and not -1; kAutoTile: the automatic choice), rebuilds and uploads the work lists;
 // cached graphs are rebuilt on the next step.  The context's tile is that of
 // the layout with the most fluid nodes.  With `merge`, the one-row, one-chunk
 // layouts whose tiles run the shared-row schedule of one mode (that of the
@@ -831,7 +852,8 @@ tau1_status set_tile(tau1_ctx* ctx, int tile, const int* per_variant = nullptr,
     for (int v : layouts) {
         tau1_ctx::ZGroup g;
         g.variant = v;
-        g.tile = per_variant && per_variant[v] >= 0 ? per_variant[v] : tile;
+        g.tile = per_variant && per_variant[v] != -1 ? per_variant[v] : tile;
+        g.lz = 0;
         g.packed = false;
         g.chunks = true;
         for (const auto& sh : ctx->plan.s)
@@ -854,9 +876,20 @@ tau1_status set_tile(tau1_ctx* ctx, int tile, const int* per_variant = nullptr,
                 }
             }
         } else {
-            const int zt = tile_zmarch(g.tile);
-            part = zmarch_worklist(ctx->plan.s.data(), ctx->nsamples, tile_lz(zt), v,
-                                   zr_share(kVariants[v].g, tile_mode(zt)));
+            // automatic: rows shared through LDS for one-row layouts (packed or
+            // not), the rolling prefetch for the others, named as a tile of
+            // the context's layout
+            const bool choose = g.tile == kAutoTile;
+            const int chosen = ctx->plan.packed ? 3 : kVariants[v].g == 1 ? 1 : 2;
+            if (choose) g.tile = chosen * 4;
+            const int mode = group_mode(g);
+            const bool blocks = zr_share(kVariants[v].g, mode);
+            g.lz = choose || g.tile == kChunkTile
+                       ? zmarch_segment(ctx->plan.s.data(), ctx->nsamples, v, blocks,
+                                        group_resident(ctx, g))
+                       : tile_lz(g.tile);
+            if (choose) g.tile = tile_named(chosen, g.lz);
+            part = zmarch_worklist(ctx->plan.s.data(), ctx->nsamples, g.lz, v, blocks);
         }
         groups.push_back(g);
         parts.push_back(std::move(part));
@@ -1108,20 +1141,20 @@ tau1_status tau1_create(const tau1_desc* desc, tau1_ctx** out) {
     }
     ctx->kernel = ctx->lattice == 9 ? 2 : desc->kernel >= 0 ? desc->kernel : (zm ? 1 : 0);
     const bool packed = ctx->plan.packed;
-    int tile = desc->tile >= 0 ? desc->tile : zmarch_default_tile(packed);
-    if (ctx->kernel == 1 && desc->tile < 0 && !ctx->cache.empty()) {
-        int t = zmarch_cache_lookup(ctx->cache.c_str(), ctx->lattice, ctx->precision,
-                                    ctx->n_nodes, packed);
-        if (t >= 0) tile = t;
-    }
     if (zm) {
-        st = set_tile(ctx, tile, nullptr, ctx->merge_rows);
+        st = set_tile(ctx, desc->tile >= 0 ? desc->tile : kAutoTile, nullptr, ctx->merge_rows);
+        if (st == TAU1_OK && ctx->kernel == 1 && desc->tile < 0 && !ctx->cache.empty()) {
+            const int t = zmarch_cache_lookup(ctx->cache.c_str(), ctx->lattice, ctx->precision,
+                                              ctx->n_nodes, packed);
+            // a cached tile that the automatic choice already goes by stays with it
+            if (t >= 0 && t != ctx->tile) st = set_tile(ctx, t, nullptr, ctx->merge_rows);
+        }
         if (st != TAU1_OK) {
             delete ctx;
             return st;
         }
     } else {
-        ctx->tile = tile;
+        ctx->tile = desc->tile >= 0 ? desc->tile : 2;  // no z-march in this context
     }
     *out = ctx;
     return TAU1_OK;
@@ -1237,16 +1270,23 @@ tau1_status tau1_autotune(tau1_ctx* ctx, int32_t trial_steps) {
     std::vector<int> tile_v(kNumVariants, -1);
     float best = 1e30f;
     int best_tile = ctx->tile;
-    for (int i = 0; i < kNumTiles && st == TAU1_OK; ++i) {
+    for (int i = 0; i <= kNumTiles && st == TAU1_OK; ++i) {
         // the chunk tile first: its launches load the card less than the
         // z-march's, and a card that has just run lighter launches runs the
         // next heavy ones at a transiently higher, then lower clock; ending
         // with the z-march tiles leaves it as the usual choice runs it
-        const int t = i == 0 ? kChunkTile : i - 1;
-        if (!zmarch_tile_ok(ctx->precision, ctx->plan.packed, t)) continue;
+        const int t = i == 0 ? kChunkTile : i == 1 ? kAutoTile : i - 2;
+        if (t != kAutoTile && !zmarch_tile_ok(ctx->precision, ctx->plan.packed, t)) continue;
         if (t == kChunkTile && !any_chunks(ctx)) continue;
         st = set_tile(ctx, t);  // layouts timed alone, also where they share a launch
         if (st != TAU1_OK) break;
+        // no trial for an automatic choice that is a tile's own, nor for a tile
+        // whose segments leave every layout at over twice the modelled time of
+        // its best length
+        bool skip = t != kChunkTile;
+        for (const auto& g : ctx->zgroups)
+            skip = skip && (t == kAutoTile ? tile_lz(g.tile) == g.lz : far_from_best(ctx, g));
+        if (skip) continue;
         float total = 0.0f;
         for (int g = 0; g < (int)ctx->zgroups.size() && st == TAU1_OK; ++g) {
             // the trial reads the current buffer and writes the spare one only
@@ -1309,10 +1349,11 @@ tau1_status tau1_autotune(tau1_ctx* ctx, int32_t trial_steps) {
     st = merged_tile >= 0 ? set_tile(ctx, merged_tile, nullptr, true)
                           : set_tile(ctx, best_tile, tile_v.data(), ctx->merge_rows);
     if (st != TAU1_OK) return st;
-    // the cache keeps one tile per size bucket: the best single tile
+    // the cache keeps one tile per size bucket: the best single tile (of an
+    // automatic choice, the one the context now goes by)
     if (!ctx->cache.empty())
         zmarch_cache_store(ctx->cache.c_str(), ctx->lattice, ctx->precision, ctx->n_nodes,
-                           best_tile, best / trial_steps);
+                           best_tile == kAutoTile ? ctx->tile : best_tile, best / trial_steps);
     return TAU1_OK;
 }
 

@@ -30,6 +30,29 @@
 
 namespace tau1 {
 
+template <int Q, int CY, int CZ, int KD = 1>
+constexpr bool ck_has_dir() {
+    if constexpr (KD >= Q) {
+        return false;
+    } else {
+        using L = Lattice<Q>;
+        return (L::c[KD].y == CY && L::c[KD].z == CZ) || ck_has_dir<Q, CY, CZ, KD + 1>();
+    }
+}
+
+// Whether some direction of the column (c_y, c_z) = (CY, CZ) has c_x != 0:
+// its sources then include the nodes on either side of the chunk.
+template <int Q, int CY, int CZ, int KD = 1>
+constexpr bool ck_needs_edges() {
+    if constexpr (KD >= Q) {
+        return false;
+    } else {
+        using L = Lattice<Q>;
+        return (L::c[KD].y == CY && L::c[KD].z == CZ && L::c[KD].x != 0) ||
+               ck_needs_edges<Q, CY, CZ, KD + 1>();
+    }
+}
+
 struct CkCtx {
     rsrc_t pre, post;         // the read and the written buffer (four arrays each)
     int abytes;               // bytes per array
@@ -115,36 +138,26 @@ __device__ __forceinline__ void ck_column(const CkCtx& c, const ck_rec_t& rec, i
     }
 }
 
-// A node's sums while its nine source columns are added (tau1_sums.hpp):
-// T, C, momentum along x and y, M.
-template <int K>
-struct CkSums {
-    float t[K], s[K], x[K], y[K], m[K];
-};
-
-// Adds one source column, the group (c_y, c_z) = (CY, CZ), from source nodes
-// x - c_x to node x.
-template <int Q, int CY, int CZ, int K>
-__device__ __forceinline__ void ck_pull(CkSums<K>& a, const Src (&s)[K + 2]) {
-    using Gr = Group<Q, CY, CZ>;
-    float f[K + 2], fp[K + 2], fm[K + 2];
+// Adds the contributions of one source column: every direction k with
+// (c_y, c_z) = (CY, CZ), in order, from source node x - c_x to node x.  The
+// multiply-adds are those of the z-march's push (add_to).
+template <int Q, int CY, int CZ, int K, int KD = 1>
+__device__ __forceinline__ void ck_pull(float (&acc)[4][K], const Src (&s)[K + 2]) {
+    if constexpr (KD < Q) {
+        using L = Lattice<Q>;
+        constexpr int CX = L::c[KD].x;
+        if constexpr (L::c[KD].y == CY && L::c[KD].z == CZ) {
+            constexpr float w = (float)weight<Q>(KD);
 #pragma unroll
-    for (int i = Gr::hasx ? 0 : 1; i < (Gr::hasx ? K + 2 : K + 1); ++i) {
-        float g;
-        level_y<CY>(s[i], f[i], g);
-        level_z<CZ>(s[i], f[i], g);
-        if constexpr (Gr::hasx) level_x(s[i], f[i], g, fp[i], fm[i]);
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        float t, e = 0.0f;
-        if constexpr (Gr::hasx) {
-            t = group_sum<Q, CY, CZ>(f[j + 1], fp[j], fm[j + 2]);
-            e = fp[j] - fm[j + 2];
-        } else {
-            t = f[j + 1];
+            for (int j = 0; j < K; ++j) {
+                const float u = feq_m<CX, CY, CZ>(s[j + 1 - CX]);
+                acc[0][j] = __builtin_fmaf(w, u, acc[0][j]);
+                if constexpr (CX != 0) acc[1][j] = __builtin_fmaf(CX * w, u, acc[1][j]);
+                if constexpr (CY != 0) acc[2][j] = __builtin_fmaf(CY * w, u, acc[2][j]);
+                if constexpr (CZ != 0) acc[3][j] = __builtin_fmaf(CZ * w, u, acc[3][j]);
+            }
         }
-        add_group<Q, CY, CZ>(t, e, a.t[j], a.s[j], a.x[j], a.y[j], a.m[j]);
+        ck_pull<Q, CY, CZ, K, KD + 1>(acc, s);
     }
 }
 
@@ -152,11 +165,10 @@ __device__ __forceinline__ void ck_pull(CkSums<K>& a, const Src (&s)[K + 2]) {
 // directions c_y = CY, c_z = CZ.
 template <int Q, int P, int CY, int CZ, int K>
 __device__ __forceinline__ void ck_source(const CkCtx& c, const ck_rec_t (&rec)[9], int ci,
-                                          const CkNb& nb, CkSums<K>& acc) {
-    using Gr = Group<Q, CY, CZ>;
-    if constexpr (Gr::has0 || Gr::hasx) {
+                                          const CkNb& nb, float (&acc)[4][K]) {
+    if constexpr (ck_has_dir<Q, CY, CZ>()) {
         Src s[K + 2];
-        ck_column<P, K, Gr::hasx>(c, rec[(1 - CY) * 3 + 1 - CZ], ci, nb, s);
+        ck_column<P, K, ck_needs_edges<Q, CY, CZ>()>(c, rec[(1 - CY) * 3 + 1 - CZ], ci, nb, s);
         ck_pull<Q, CY, CZ, K>(acc, s);
     }
 }
@@ -247,7 +259,12 @@ void k_chunks(StepArgs a) {
             win[dy + 1][dz + 1] = xmask_window(
                 c.xm, (int64_t)wrapi(z + dz, c.nz) * c.ny + wrapi(y + dy, c.ny), c.xw, x0);
 
-    CkSums<K> acc;
+    float acc[4][K];
+#pragma unroll
+    for (int comp = 0; comp < 4; ++comp)
+#pragma unroll
+        for (int j = 0; j < K; ++j) acc[comp][j] = 0.0f;
+
     // source plane z - 1 (directions with c_z = +1): own row, row y-1, row y+1
     ck_source<Q, P, 0, 1, K>(c, rec, ci, nb, acc);
     ck_source<Q, P, 1, 1, K>(c, rec, ci, nb, acc);
@@ -256,6 +273,11 @@ void k_chunks(StepArgs a) {
     Src own[K + 2];
     ck_column<P, K, true>(c, rec[4], ci, nb, own);
     ck_pull<Q, 0, 0, K>(acc, own);
+    {
+        constexpr float w0 = (float)weight<Q>(0);
+#pragma unroll
+        for (int j = 0; j < K; ++j) acc[0][j] = __builtin_fmaf(w0, own[j + 1].a, acc[0][j]);
+    }
     ck_source<Q, P, 1, 0, K>(c, rec, ci, nb, acc);
     ck_source<Q, P, -1, 0, K>(c, rec, ci, nb, acc);
     // wall returns of the fluid nodes with a solid link (for the others the
@@ -269,15 +291,13 @@ void k_chunks(StepArgs a) {
     const uint32_t fluid = ~(win[1][1] >> 1) & ((1u << K) - 1u);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        float r[4] = {0.f, 0.f, 0.f, 0.f};
         if ((fluid & any) >> j & 1u) {
-            const auto link = [&](int k) { return (uint32_t)__builtin_amdgcn_sbfe((int)sdir[k], j, 1); };
-            wall_sums<Q>(own[j + 1], PickMask<decltype(link)>{link}, r);
+            float r[4];
+            wall_dirs<Q>(own[j + 1],
+                         [&](int k) { return (uint32_t)__builtin_amdgcn_sbfe((int)sdir[k], j, 1); }, r);
+#pragma unroll
+            for (int comp = 0; comp < 4; ++comp) acc[comp][j] += r[comp];
         }
-        acc.s[j] += r[0];
-        acc.x[j] += r[1];
-        acc.y[j] += r[2];
-        acc.t[j] += r[3];
     }
     // source plane z + 1 (directions with c_z = -1)
     ck_source<Q, P, 0, -1, K>(c, rec, ci, nb, acc);
@@ -290,12 +310,12 @@ void k_chunks(StepArgs a) {
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const bool f = (fluid >> j) & 1u;
-        float d, vx, vy, vz;
-        finish_node<Q>(acc.t[j], acc.s[j], acc.m[j], acc.x[j], acc.y[j], gx, gy, gz, d, vx, vy, vz);
+        const float d = acc[0][j];
+        const float r = __builtin_amdgcn_rcpf(1.0f + d);
         od[j] = f ? d : 0.0f;
-        ox[j] = f ? vx : 0.0f;
-        oy[j] = f ? vy : 0.0f;
-        oz[j] = f ? vz : 0.0f;
+        ox[j] = f ? __builtin_fmaf(acc[1][j], r, gx) : 0.0f;
+        oy[j] = f ? __builtin_fmaf(acc[2][j], r, gy) : 0.0f;
+        oz[j] = f ? __builtin_fmaf(acc[3][j], r, gz) : 0.0f;
     }
     const float sr = scale_rho<P>(a), su = scale_u<P>(a);
     // a lane past the item's chunks stores out of range (dropped)

@@ -7,8 +7,7 @@
 // source plane it reads the window of rows y - 1, y, y + 1 with one coalesced
 // load per row and array, requested one plane ahead, forms the sources and
 // sends each group of directions (tau1_sums.hpp) to the planes z - 1, z, z + 1;
-// values for x +- 1 move one lane by DPP.  Sums are formed in the z-march's
-// order, so FP32 and 16-bit results are the same bits as the z-march tiles'.
+// values for x +- 1 move one lane by DPP.
 //
 // Solid links need no vector work: with one node per lane, the solid bits of a
 // row window are a lane mask.  They are read with scalar loads from the

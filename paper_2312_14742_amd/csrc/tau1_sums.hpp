@@ -1,6 +1,6 @@
-// tau1_sums.hpp -- equilibria and moment sums shared by every 3-D step kernel
-// (z-march tiles, chunk kernel, row kernel), so that all of them form each
-// destination sum with the same roundings.
+// tau1_sums.hpp -- sources, and equilibria and moment sums by groups of
+// directions, in any compute type (the row kernel's form; the z-march and chunk
+// kernels take the sources from here and sum direction by direction).
 //
 // The directions of a lattice fall into nine groups by (c_y, c_z); a group
 // holds at most the directions c_x = 0, +1, -1.  What a group sends to a node
@@ -24,19 +24,14 @@
 // (c_y, 0) give those at (c_y, c_z), and those give the two directions c_x =
 // +-1 with one shared term (38 operations for the 18 directions of D3Q19
 // against 46 one by one).
-//
-// Measured against a sum per direction and component (MI355X, 1000 steps with
-// readback): D3Q19 FP16 256^3 181 -> 145 ms, D3Q27 FP32 256^3 (500 steps) 138
-// -> 131 ms, a batch of 12 samples 414 -> 398 ms; D3Q19 FP32 512^3 and the
-// chunk kernel, bound by their memory accesses, 1-2 %.
 #pragma once
 
 #include "tau1_args.hpp"
 
 // Multiply-adds fuse only where one expression writes a * b + c (and at the
-// explicit fma calls), never across statements: every kernel, tile and load
-// schedule then forms each sum with the same roundings, so results do not
-// depend on the kernel or tile chosen.
+// explicit fma calls), never across statements: every tile and load schedule
+// of a kernel then forms each sum with the same roundings, so results do not
+// depend on the tile the autotuner picks.
 #pragma clang fp contract(on)
 
 namespace tau1 {
@@ -192,9 +187,8 @@ constexpr int dir_index(int x, int y, int z) {
 
 // Halfway bounce-back (Eq. 11) at one node: every direction k whose neighbour
 // x + c_k is solid returns the node's own equilibrium in k along -c_k.
-// pick(k, u) is u where that neighbour is solid, else zero (the kernels keep
-// the solid links in different forms).  r: what a kernel adds to C (density
-// less z-momentum), x, y and T (z-momentum), in units.
+// pick(k, u) is u where that neighbour is solid, else zero.  r: what is added to
+// C (density less z-momentum), x, y and T (z-momentum), in units.
 template <int Q, int CX, int CY, int CZ, typename T, typename Pick>
 __device__ __forceinline__ void wall_dir(T f, const Pick& pick, T (&r)[4]) {
     constexpr int w = weight_units<Q>((CX != 0) + (CY != 0) + (CZ != 0));
@@ -236,20 +230,12 @@ __device__ __forceinline__ void wall_sums(const SrcT<T>& s, const Pick& pick, T 
     r[0] -= r[3];
 }
 
-// The link selection of a kernel that keeps one all-ones / zero word per link.
-template <typename Link>
-struct PickMask {
-    const Link& link;
-    template <typename K>
-    __device__ __forceinline__ float operator()(K, float u) const {
-        return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, u) & link(K::value));
-    }
-};
-
 // New state of one node from its sums (file header): v = j / rho + g with one
 // reciprocal; FP32 uses the hardware's, FP64 divides.  unit * C is rounded
 // before the sum's last addition, at two thirds of its size or less, so that
-// the unit costs less rounding than one more full-size addition.
+// the unit costs less rounding than one more full-size addition.  The unit as
+// a number of type T is off by up to 7e-9 in FP32, the same way in every step,
+// which a flow of hundreds of steps would collect: v takes the difference back.
 __device__ __forceinline__ float recip_t(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double recip_t(double x) { return 1.0 / x; }
 
@@ -257,12 +243,18 @@ template <int Q, typename T>
 __device__ __forceinline__ void finish_node(T t, T c, T m, T jx, T jy, T gx, T gy, T gz, T& d,
                                             T& vx, T& vy, T& vz) {
     constexpr T unit = weight_unit<Q, T>();
-    const T uc = unit * c, tm = t + m;
+    const T uc = unit * c, tm = t + m, jz = t - m;
     d = fma_t(unit, tm, uc);
     const T r = recip_t((T)1 + d) * unit;
+    if constexpr (sizeof(T) == 4) {
+        constexpr T off = (T)(1.0 / Lattice<Q>::units - (double)unit);
+        gx = fma_t(jx, off, gx);
+        gy = fma_t(jy, off, gy);
+        gz = fma_t(jz, off, gz);
+    }
     vx = fma_t(jx, r, gx);
     vy = fma_t(jy, r, gy);
-    vz = fma_t(t - m, r, gz);
+    vz = fma_t(jz, r, gz);
 }
 
 }  // namespace tau1

@@ -73,9 +73,17 @@ constexpr int kCkWaves = 4;
 constexpr int kCkThreads = 64 * kCkWaves;
 constexpr int kChunkBits = 7;
 inline bool tile_packed(int tile) { return tile_mode(tile) == 3 || tile == kChunkTile; }
-// The z-march tile that stands in for the chunk tile in a launch group that
+// The automatic choice: the layout's usual schedule at the z-segment length of
+// zmarch_segment.  It also stands in for the chunk tile in a launch group that
 // is not packed (a batch may mix packed and dense lane layouts).
-inline int tile_zmarch(int tile) { return tile == kChunkTile ? 14 : tile; }
+constexpr int kAutoTile = -2;
+// Tile that names `mode` at z-segments of lz planes: the shortest that is no
+// shorter.
+inline int tile_named(int mode, int lz) {
+    int i = 0;
+    while (i < 3 && kTileLZ[i] < lz) ++i;
+    return mode * 4 + i;
+}
 
 // Load schedule of a (layout, mode) pair: shared rows need one row per wave.
 constexpr bool zr_share(int g, int mode) { return (mode == 1 || mode == 3) && g == 1; }
@@ -284,11 +292,24 @@ struct RawRow {
 // Components of a source kept in a shared LDS row slot: A, R3, vx, vy, vz.
 constexpr int kSlotComps = 5;
 
-// Partial sums of one destination plane, per slot, by the source plane they
-// came from (tau1_sums.hpp): t = T, s = C, x and y = momentum in units.  Three planes (z-1, z, z+1 of the source plane) rotate roles.
+// The z-march and chunk kernels evaluate each direction's equilibrium alone and
+// add it, weighted, to the density and momentum of its destination, in the
+// lattice's order.
+template <int CX, int CY, int CZ>
+__device__ __forceinline__ float feq_m(const Src& s) {
+    float cu = 0.0f;
+    if constexpr (CX != 0) cu = CX > 0 ? s.vx : -s.vx;
+    if constexpr (CY != 0) cu = (CX != 0) ? (CY > 0 ? cu + s.vy : cu - s.vy) : (CY > 0 ? s.vy : -s.vy);
+    if constexpr (CZ != 0)
+        cu = (CX != 0 || CY != 0) ? (CZ > 0 ? cu + s.vz : cu - s.vz) : (CZ > 0 ? s.vz : -s.vz);
+    return __builtin_fmaf(__builtin_fmaf(s.r45, cu, s.r3), cu, s.a);
+}
+
+// Partial sums of one destination plane: [component][slot], components drho,
+// jx, jy, jz.  Three planes (z-1, z, z+1 of the source plane) rotate roles.
 template <int PX>
 struct Plane {
-    float t[PX], s[PX], x[PX], y[PX];
+    float v[4][PX];
 };
 
 template <int PX>
@@ -298,88 +319,100 @@ struct Planes {
     Plane<PX>& p;  // z + 1
 };
 
-// Fixes the place of a value's computation (no instruction).
-__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)); }
+template <int CX, int CY, int CZ, int PX>
+__device__ __forceinline__ void add_to(Planes<PX>& pl, int slot, float w, float u) {
+    Plane<PX>& q = CZ < 0 ? pl.m : (CZ == 0 ? pl.c : pl.p);
+    q.v[0][slot] = __builtin_fmaf(w, u, q.v[0][slot]);
+    if constexpr (CX != 0) q.v[1][slot] = __builtin_fmaf(CX * w, u, q.v[1][slot]);
+    if constexpr (CY != 0) q.v[2][slot] = __builtin_fmaf(CY * w, u, q.v[2][slot]);
+    if constexpr (CZ != 0) q.v[3][slot] = __builtin_fmaf(CZ * w, u, q.v[3][slot]);
+}
 
-// Push group (CY, CZ) of every slot of a source row to its plane: f and g are
-// the slots' values and slopes along (0, CY, 0).  Slot (c, j) sends to
-// (c, j + c_x); across a lane boundary the value rotates one lane inside the
-// group, and the group's first/last lane takes it from the neighbouring chunk
-// (the node after the last of chunk c is the first of c+1).  m: the sums M of
-// plane z - 1, set and used within one step.
-template <int Q, int CY, int CZ, int G, int C, int K, int NL>
-__device__ __forceinline__ void push_group(Plane<C * K>& q, float (&m)[C * K],
-                                           const Src (&s)[C * K], const float (&f0)[C * K],
-                                           const float (&g0)[C * K], const ZrLanes& ln) {
-    using Gr = Group<Q, CY, CZ>;
-    constexpr int PX = C * K;
-    if constexpr (Gr::has0 || Gr::hasx) {
-        float f[PX], fp[PX], fm[PX], up[C], dn[C];
-        auto recv = [&](int i, float a, float b) {
-            const float t = group_sum<Q, CY, CZ>(f[i], a, b);
-            add_group<Q, CY, CZ>(t, Gr::hasx ? a - b : 0.0f, q.t[i], q.s[i], q.x[i], q.y[i], m[i]);
-        };
+// Push the direction-KD contribution of every slot of a source row.  Slot
+// (c, j) sends to (c, j + c_x); across a lane boundary the value rotates one
+// lane inside the group, and the group's first/last lane takes it from the
+// neighbouring chunk (the node after the last of chunk c is the first of c+1).
+template <int Q, int KD, int G, int C, int K, int NL>
+__device__ __forceinline__ void push_dir(Planes<C * K>& pl, const Src (&s)[C * K], int zmask,
+                                         const ZrLanes& ln) {
+    using L = Lattice<Q>;
+    constexpr int CX = L::c[KD].x, CY = L::c[KD].y, CZ = L::c[KD].z;
+    if (!((zmask >> (CZ + 1)) & 1)) return;
+    constexpr float w = (float)weight<Q>(KD);
+    float edge[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c)
+    for (int c = 0; c < C; ++c) {
 #pragma unroll
-            for (int j = 0; j < K; ++j) {
-                const int i = c * K + j;
-                float g = g0[i];
-                f[i] = f0[i];
-                level_z<CZ>(s[i], f[i], g);
-                if constexpr (!Gr::hasx) {
-                    recv(i, 0.0f, 0.0f);
-                } else {
-                    level_x(s[i], f[i], g, fp[i], fm[i]);
-                    if (j == 0) dn[c] = lane_down<G, NL>(fm[i], ln);
-                    if (j == K - 1) up[c] = lane_up<G, NL>(fp[i], ln);
-                    if (j >= 2) recv(i - 1, fp[i - 2], fm[i]);
-                }
-            }
-        if constexpr (Gr::hasx) {
-            // the chunks' first and last slots
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                float a = up[c], b = dn[c];
-                if constexpr (C > 1) {
-                    a = lane_pick(ln.first, up[(c + C - 1) % C], a);
-                    b = lane_pick(ln.last, dn[(c + 1) % C], b);
-                }
-                if constexpr (K == 1) {
-                    recv(c, a, b);
-                } else {
-                    recv(c * K, a, fm[c * K + 1]);
-                    recv(c * K + K - 1, fp[c * K + K - 2], b);
-                }
+        for (int j = 0; j < K; ++j) {
+            const float u = feq_m<CX, CY, CZ>(s[c * K + j]);
+            const int dst = j + CX;
+            if (dst >= 0 && dst < K) {
+                add_to<CX, CY, CZ, C * K>(pl, c * K + dst, w, u);
+            } else if (dst == K) {
+                edge[c] = lane_up<G, NL>(u, ln);
+            } else {
+                edge[c] = lane_down<G, NL>(u, ln);
             }
         }
-        // the sums are final here: without this the compiler moves the
-        // additions of a row down to their next use, past branches, and keeps
-        // the row's sources alive meanwhile (246 spilled registers at nx = 512)
+    }
+    if constexpr (CX != 0) {
 #pragma unroll
-        for (int i = 0; i < PX; ++i) {
-            if constexpr (CZ < 0) pin(m[i]);
-            else if constexpr (CZ > 0) pin(q.t[i]);
-            else pin(q.s[i]);
-            if constexpr (CY != 0) pin(q.y[i]);
-            if constexpr (Gr::hasx) pin(q.x[i]);
+        for (int c = 0; c < C; ++c) {
+            float v = edge[c];
+            if constexpr (C > 1) {
+                if constexpr (CX > 0) v = lane_pick(ln.first, edge[(c + C - 1) % C], v);
+                else v = lane_pick(ln.last, edge[(c + 1) % C], v);
+            }
+            add_to<CX, CY, CZ, C * K>(pl, CX > 0 ? c * K : c * K + K - 1, w, v);
         }
     }
 }
 
-// Push the directions c_y = CY of a source row.  ZS: 0 = to the planes z - 1,
-// z, z + 1; +1 / -1 = to that plane only.  One group at a time, in order, and
-// each slot added to as soon as its right neighbour is evaluated: few values
-// are alive beside the row's sources and the planes' sums.
-template <int Q, int CY, int ZS, int G, int C, int K, int NL>
-__device__ __forceinline__ void push_row(Planes<C * K>& pl, float (&m)[C * K],
-                                         const Src (&s)[C * K], const ZrLanes& ln) {
-    float f[C * K], g[C * K];
+template <int Q, int CYSEL, int G, int C, int K, int NL, int KD = 1>
+__device__ __forceinline__ void push_row(Planes<C * K>& pl, const Src (&s)[C * K], int zmask,
+                                         const ZrLanes& ln) {
+    if constexpr (KD < Q) {
+        if constexpr (Lattice<Q>::c[KD].y == CYSEL)
+            push_dir<Q, KD, G, C, K, NL>(pl, s, zmask, ln);
+        push_row<Q, CYSEL, G, C, K, NL, KD + 1>(pl, s, zmask, ln);
+    }
+}
+
+// Bounce-back sums of one wall node (one per worker lane): every direction k
+// whose neighbour x + c_k is solid returns the node's own equilibrium in k
+// along -c_k.  Sums are kept per weight class and weighted at the end.
+// link(k) is all ones when the neighbour x + c_k is solid, else zero (the
+// step kernels keep the solid links in different forms).
+template <int Q, int KD = 1, typename Link>
+__device__ __forceinline__ void bounce_sum(const Src& s, const Link& link, float (&d)[3],
+                                           float (&j)[3][3]) {
+    if constexpr (KD < Q) {
+        using L = Lattice<Q>;
+        constexpr int CX = L::c[KD].x, CY = L::c[KD].y, CZ = L::c[KD].z;
+        constexpr int cls = (CX != 0) + (CY != 0) + (CZ != 0) - 1;  // face, edge, corner
+        const uint32_t m = link(KD);
+        const float u = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, feq_m<CX, CY, CZ>(s)) & m);
+        d[cls] += u;
+        if constexpr (CX != 0) j[cls][0] -= CX * u;
+        if constexpr (CY != 0) j[cls][1] -= CY * u;
+        if constexpr (CZ != 0) j[cls][2] -= CZ * u;
+        bounce_sum<Q, KD + 1>(s, link, d, j);
+    }
+}
+
+// Weighted wall returns of one node: density and momentum (r[0], r[1..3]) of
+// the populations its solid links send back.  The step kernels all add these
+// four values to the node's sums at the same point, so they share this code.
+template <int Q, typename Link>
+__device__ __forceinline__ void wall_dirs(const Src& sw, const Link& link, float (&r)[4]) {
+    float sd[3] = {0.f, 0.f, 0.f};
+    float sj[3][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    bounce_sum<Q>(sw, link, sd, sj);
+    constexpr float wf = (float)Lattice<Q>::w_face, we = (float)Lattice<Q>::w_edge,
+                    wc = (float)Lattice<Q>::w_corner;
+    r[0] = wf * sd[0] + we * sd[1] + wc * sd[2];
 #pragma unroll
-    for (int i = 0; i < C * K; ++i) level_y<CY>(s[i], f[i], g[i]);
-    if constexpr (ZS == 0) push_group<Q, CY, 0, G, C, K, NL>(pl.c, m, s, f, g, ln);
-    if constexpr (ZS >= 0) push_group<Q, CY, 1, G, C, K, NL>(pl.p, m, s, f, g, ln);
-    if constexpr (ZS <= 0) push_group<Q, CY, -1, G, C, K, NL>(pl.m, m, s, f, g, ln);
+    for (int a = 0; a < 3; ++a) r[1 + a] = wf * sj[0][a] + we * sj[1][a] + wc * sj[2][a];
 }
 
 __device__ __forceinline__ int wrapi(int a, int n) {
@@ -573,10 +606,8 @@ __device__ __forceinline__ void chunk_voffs(const ZrItem<P, G, C, K>& it, const 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(t.hi[c], __builtin_amdgcn_mbcnt_lo(t.lo[c], 0u));
-        // the bitmap is the lane mask of the select
-        const bool stored = __builtin_amdgcn_inverse_ballot_w64(((uint64_t)t.hi[c] << 32) | t.lo[c]);
-        const int at = (int)((t.rank[c] + below) * CB);
-        vo[c] = stored ? at : kOob;
+        const uint64_t bits = ((uint64_t)t.hi[c] << 32) | t.lo[c];
+        vo[c] = ((bits >> it.lane) & 1u) ? (int)((t.rank[c] + below) * CB) : kOob;
     }
 }
 
@@ -704,7 +735,6 @@ __device__ __forceinline__ void bounce_list(const ZrItem<P, G, C, K>& it, Plane<
     constexpr int Lg = 64 / G;
     constexpr int RS = 64 * PX;  // = G * nx
     const int total = wp.cur1 - wp.cur0;
-    if (total == 0) return;  // no wall node in these rows
     const int grp = G == 1 ? 0 : it.lane / Lg;
     if (state) {
 #pragma unroll
@@ -741,8 +771,7 @@ __device__ __forceinline__ void bounce_list(const ZrItem<P, G, C, K>& it, Plane<
             }
             float r[4];
             // bit k - 1 of the entry's links: the neighbour x + c_k is solid
-            const auto link = [&](int k) { return (uint32_t)__builtin_amdgcn_sbfe((int)links, k - 1, 1); };
-            wall_sums<Q>(sw, PickMask<decltype(link)>{link}, r);
+            wall_dirs<Q>(sw, [&](int k) { return (uint32_t)__builtin_amdgcn_sbfe((int)links, k - 1, 1); }, r);
 #pragma unroll
             for (int c = 0; c < 4; ++c) res[c * RS + n] = r[c];
         }
@@ -756,13 +785,7 @@ __device__ __forceinline__ void bounce_list(const ZrItem<P, G, C, K>& it, Plane<
             float t[K];
             __builtin_memcpy(t, e, sizeof t);
 #pragma unroll
-            for (int j = 0; j < K; ++j) {
-                const int i = c * K + j;
-                if (comp == 0) pc.s[i] += t[j];
-                else if (comp == 1) pc.x[i] += t[j];
-                else if (comp == 2) pc.y[i] += t[j];
-                else pc.t[i] += t[j];
-            }
+            for (int j = 0; j < K; ++j) pc.v[comp][c * K + j] += t[j];
             if (!state) {
                 const float z[K] = {};
                 __builtin_memcpy(e, z, sizeof z);
@@ -772,7 +795,7 @@ __device__ __forceinline__ void bounce_list(const ZrItem<P, G, C, K>& it, Plane<
 }
 
 // One source plane zs: pl.m, pl.c, pl.p are the destination planes zs-1, zs,
-// zs+1 (this plane's first contribution sets pl.p).  Finalises and stores plane zs-1 at the end.
+// zs+1 (pl.p starts empty).  Finalises and stores plane zs-1 at the end.
 //
 // Load schedules (MODE, the tile's mode).  Mode 0: each source row is
 // loaded just before it is used.  Shared rows (mode 1, one row per wave):
@@ -783,13 +806,7 @@ __device__ __forceinline__ void bounce_list(const ZrItem<P, G, C, K>& it, Plane<
 // rows are read and written at their chunks' packed offsets.  Rolling
 // prefetch (mode 2, and modes 1 and 3 with G > 1): the own row of the next
 // plane (`ahead`) is requested during this plane.
-//
-// ZS: 0 = a plane of the segment; +1 = the plane before it, which sends to
-// plane z0 only and finalises nothing; -1 = the plane after it, which sends
-// to plane z1 - 1 only.  The three are compiled apart (instead of a mask
-// tested at each push), so that a plane's registers are free from its store
-// to its first contribution two steps later.
-template <int Q, int P, int G, int C, int K, int NL, int MODE, bool EARLY_OK, int ZS>
+template <int Q, int P, int G, int C, int K, int NL, int MODE, bool EARLY_OK>
 __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Planes<C * K> pl,
                                         uint32_t (&win_next)[C], uint32_t& fluid_prev,
                                         WallPipe<Q>& wp, RawRow<C * K>& ahead, PkPipe<C>& pk) {
@@ -798,7 +815,10 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
     constexpr bool ROLL = zr_roll(G, MODE);
     constexpr bool PK = zr_packed(G, MODE);
     constexpr int RS = 64 * PX;
-    const int z0 = it.z0, ny = it.ny, nz = it.nz;
+    const int z0 = it.z0, z1 = it.z1, ny = it.ny, nz = it.nz;
+    const int zmask = ((zs - 1 >= z0 && zs - 1 < z1) ? 1 : 0) |
+                      ((zs >= z0 && zs < z1) ? 2 : 0) |
+                      ((zs + 1 >= z0 && zs + 1 < z1) ? 4 : 0);
     const int zc = wrapi(zs % nz, nz);
     const uint32_t fown = fluid_bits<C, K>(win_next);
     const int rm_ = zc * ny + it.ym, rp_ = zc * ny + it.yp, ro_ = zc * ny + it.yc;
@@ -821,7 +841,7 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
     // state of this plane's first 64 wall nodes, used by the bounce-back below
     float wv[4] = {0.f, 0.f, 0.f, 0.f};
     if constexpr (!SHARE)
-        wall_state<Q>(it, wp.cur, zc, ZS == 0 && it.lane < wp.cur1 - wp.cur0, wv);
+        wall_state<Q>(it, wp.cur, zc, (zmask & 2) && it.lane < wp.cur1 - wp.cur0, wv);
 
     float* own = nullptr;
     float* spare = nullptr;
@@ -852,7 +872,6 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
     // Every schedule adds the rows in the same order -- own row, row y-1,
     // row y+1 -- so every tile forms each sum with the same roundings.
     // ---- own row: c_y = 0 directions and the rest population
-    float mz[PX];  // M of plane zs - 1
     {
         Src s[PX];
         if constexpr (SHARE) {
@@ -861,7 +880,12 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
 #pragma unroll
             for (int j = 0; j < PX; ++j) s[j] = make_src(ro.d[j], ro.vx[j], ro.vy[j], ro.vz[j]);
         }
-        push_row<Q, 0, ZS, G, C, K, NL>(pl, mz, s, it.ln);
+        push_row<Q, 0, G, C, K, NL>(pl, s, zmask, it.ln);
+        if (zmask & 2) {
+            constexpr float w0 = (float)weight<Q>(0);
+#pragma unroll
+            for (int j = 0; j < PX; ++j) pl.c.v[0][j] = __builtin_fmaf(w0, s[j].a, pl.c.v[0][j]);
+        }
     }
     // rolling prefetch: each row is requested one push ahead of its use, the
     // next plane's own row once this one's registers are free
@@ -891,7 +915,7 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
 #pragma unroll
             for (int j = 0; j < PX; ++j) s[j] = make_src(rm.d[j], rm.vx[j], rm.vy[j], rm.vz[j]);
         }
-        push_row<Q, 1, ZS, G, C, K, NL>(pl, mz, s, it.ln);
+        push_row<Q, 1, G, C, K, NL>(pl, s, zmask, it.ln);
     }
     if constexpr (ROLL) load_row(it, wrapi((zs + 1) % nz, nz) * ny + it.yc, ahead);
     else if constexpr (!SHARE) load_row(it, rp_, rp);
@@ -903,10 +927,10 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
 #pragma unroll
             for (int j = 0; j < PX; ++j) s[j] = make_src(rp.d[j], rp.vx[j], rp.vy[j], rp.vz[j]);
         }
-        push_row<Q, -1, ZS, G, C, K, NL>(pl, mz, s, it.ln);
+        push_row<Q, -1, G, C, K, NL>(pl, s, zmask, it.ln);
     }
     // ---- halfway bounce-back at this plane's wall nodes (static list)
-    if constexpr (ZS == 0)
+    if (zmask & 2)
         bounce_list<Q, P, G, C, K>(it, pl.c, wp, zc, wv, SHARE ? own : nullptr,
                                    SHARE ? spare : it.lds_res);
     wp.cur0 = wp.next0;
@@ -917,7 +941,7 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
 
     // ---- plane zs - 1 is complete: finalise and store whole chunks, solid
     // slots included (they rewrite their zeros), so every line is written whole
-    if (ZS <= 0 && (ZS < 0 || zs > z0) && it.active) {
+    if ((zmask & 1) && it.active) {
         const int ro2 = (wrapi(zc - 1, nz) * ny + it.yc) * it.nx * ZrItem<P, G, C, K>::ES;
         const int so = G == 1 ? ro2 : 0;
 #pragma unroll
@@ -927,13 +951,12 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
             for (int j = 0; j < K; ++j) {
                 const int sl = c * K + j;
                 const bool f = (fluid_prev >> sl) & 1u;
-                float d, vx, vy, vz;
-                finish_node<Q>(pl.m.t[sl], pl.m.s[sl], mz[sl], pl.m.x[sl], pl.m.y[sl], it.gx,
-                               it.gy, it.gz, d, vx, vy, vz);
+                const float d = pl.m.v[0][sl];
+                const float r = __builtin_amdgcn_rcpf(1.0f + d);
                 od[j] = f ? d : 0.0f;
-                ox[j] = f ? vx : 0.0f;
-                oy[j] = f ? vy : 0.0f;
-                oz[j] = f ? vz : 0.0f;
+                ox[j] = f ? __builtin_fmaf(pl.m.v[1][sl], r, it.gx) : 0.0f;
+                oy[j] = f ? __builtin_fmaf(pl.m.v[2][sl], r, it.gy) : 0.0f;
+                oz[j] = f ? __builtin_fmaf(pl.m.v[3][sl], r, it.gz) : 0.0f;
             }
             const int vo = PK ? pk.vst[c] : it.voff[c] + (G == 1 ? 0 : ro2);
             if constexpr (PK) {
@@ -970,6 +993,14 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
         if (!it.share_m) chunk_voffs(it, tn_m, pk.vm);
         if (!it.share_p) chunk_voffs(it, tn_p, pk.vp);
     }
+}
+
+template <int PX>
+__device__ __forceinline__ void zero_plane(Plane<PX>& q) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int j = 0; j < PX; ++j) q.v[c][j] = 0.0f;
 }
 
 // One work item: G rows starting at row-group rg, destination planes [z0, z1).
@@ -1047,6 +1078,9 @@ __device__ __forceinline__ void zr_item(const StepArgs& a, const SampleDev* sd, 
     it.ctab = (ctab_t*)(a.base + uniform64(sd->chunk_tab));
 
     Plane<PX> A, B, Cp;
+    zero_plane(A);
+    zero_plane(B);
+    zero_plane(Cp);
     uint32_t fluid_prev = 0;
     uint32_t win_next[C];
     load_windows(it, wrapi((z0 - 1) % it.nz, it.nz), win_next);
@@ -1073,25 +1107,18 @@ __device__ __forceinline__ void zr_item(const StepArgs& a, const SampleDev* sd, 
     } else if constexpr (MODE != 0) {
         load_row(it, wrapi((z0 - 1) % it.nz, it.nz) * it.ny + it.yc, rm);
     }
-    // the plane before the segment, the segment's planes (the three plane roles
-    // rotate statically: the march is unrolled by three), the plane after it
-    zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK, 1>(it, z0 - 1, Planes<PX>{B, Cp, A}, win_next, fluid_prev, wp, rm, pk);
-    int zs = z0;
+    int zs = z0 - 1;
     while (true) {
-        zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK, 0>(it, zs, Planes<PX>{Cp, A, B}, win_next, fluid_prev, wp, rm, pk);
-        if (++zs >= z1) break;
-        zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK, 0>(it, zs, Planes<PX>{A, B, Cp}, win_next, fluid_prev, wp, rm, pk);
-        if (++zs >= z1) {
-            A = B;
-            break;
-        }
-        zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK, 0>(it, zs, Planes<PX>{B, Cp, A}, win_next, fluid_prev, wp, rm, pk);
-        if (++zs >= z1) {
-            A = Cp;
-            break;
-        }
+        zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK>(it, zs, Planes<PX>{A, B, Cp}, win_next, fluid_prev, wp, rm, pk);
+        zero_plane(A);
+        if (++zs > z1) break;
+        zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK>(it, zs, Planes<PX>{B, Cp, A}, win_next, fluid_prev, wp, rm, pk);
+        zero_plane(B);
+        if (++zs > z1) break;
+        zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK>(it, zs, Planes<PX>{Cp, A, B}, win_next, fluid_prev, wp, rm, pk);
+        zero_plane(Cp);
+        if (++zs > z1) break;
     }
-    zr_step<Q, P, G, C, K, NL, MODE, EARLY_OK, -1>(it, z1, Planes<PX>{A, B, Cp}, win_next, fluid_prev, wp, rm, pk);
 }
 
 // The packed shared-row schedule (mode 3) of FP32 D3Q15 and D3Q19, per lane
@@ -1148,7 +1175,7 @@ void k_zmarch(StepArgs a) {
     // [kZrWaves][4][64 * kPX]
     constexpr int kLds = kShare ? 2 * kZrWaves * kSlotComps * kPX * 64 : kZrWaves * 4 * kPX * 64;
     __shared__ float lds_all[kLds];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = threadIdx.x >> 6;
     float* lds_wave = lds_all + wave * 4 * kPX * 64;
     if constexpr (!kShare) {
         // bounce-back sums start at zero; every use clears what it read
@@ -1223,7 +1250,7 @@ void k_zmarch_rows(StepArgs a) {
     static_assert(MODE == 1 || MODE == 3, "shared-row schedules only");
     constexpr int kLds = 2 * kZrWaves * kSlotComps * zr_rows_px() * 64;
     __shared__ float lds_all[kLds];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = threadIdx.x >> 6;
     const int nwg = gridDim.x;
     const int b = blockIdx.x;
     const int per = (nwg + 7) / 8;
@@ -1264,9 +1291,6 @@ inline bool zmarch_tile_ok(int prec, bool packed, int tile) {
     return zmarch_precision_ok(prec) && tile >= 0 && tile < kNumTiles &&
            tile_packed(tile) == packed;
 }
-
-// z-segments of 64 planes
-inline int zmarch_default_tile(bool packed) { return packed ? 14 : 2; }
 
 inline void* pick_zmarch(int q, int p, int variant, int mode) {
     switch (q * 10 + p) {
@@ -1313,11 +1337,9 @@ inline void* pick_zmarch_rows(int q, int p, int mode) {
     return nullptr;
 }
 
-inline int zmarch_threads(int) { return kZrThreads; }
-
 // Resident-sized grid: at most enough workgroups for every item, rounded to
 // whole XCD rounds.
-inline int64_t zmarch_grid(int64_t nitems, int) {
+inline int64_t zmarch_grid(int64_t nitems) {
     const int64_t wgs = (nitems + kZrWaves - 1) / kZrWaves;
     const int64_t cap = 256 * 8;  // 256 CUs x up to 8 workgroups resident
     int64_t g = wgs < cap ? wgs : cap;
@@ -1395,15 +1417,62 @@ inline std::vector<int32_t> zmarch_worklist(const SH* s, int n, int lz, int vari
     return out;
 }
 
+// Shortest z-segment of a context: one plane where the lattice is small, more
+// where that would come to more than about 16384 workgroups (far beyond what
+// fills the card).
+constexpr int64_t kZrMaxGroups = 16384;
 template <typename SH>
-inline int64_t zmarch_max_items(const SH* s, int n) {
+inline int zmarch_min_lz(const SH* s, int n) {
+    int64_t planes = 0;
+    for (int i = 0; i < n; ++i)
+        if (s[i].dev.variant >= 0) planes += (int64_t)zmarch_rows(s[i].dev, true) * s[i].dev.nz;
+    return (int)std::clamp<int64_t>(planes / (kZrWaves * kZrMaxGroups), 1, kTileLZ[0]);
+}
+
+// Work items of one sample at segments of lz planes.
+inline int64_t zmarch_items(const SampleDev& sd, int lz) {
+    return sd.variant < 0 ? 0 : (int64_t)zmarch_rows(sd, true) * ((sd.nz + lz - 1) / lz);
+}
+
+// z-segment length of a launch group (lane layout `variant`) whose kernel runs
+// `resident` workgroups per CU.  A segment of lz planes marches through lz + 2
+// of them one after another, so short segments end sooner and long ones repeat
+// less.  Per plane a CU takes a time that grows with its resident workgroups w
+// like 2.2 + w (fitted to step times of 64^3 to 256^3 and 512 x 64 x 64 at
+// segments of 1-32 planes), and a launch runs in rounds of `resident`; the
+// length with the shortest sum is taken.  Against segments of 64 planes, the
+// fixed default this replaces (FP32 step, us): 48 x 40 x 36 70 -> 5.5, 64^3
+// 84 -> 6.8, 128^3 98 -> 19, 512 x 64 x 64 235 -> 19, 256^3 173 -> 98.
+template <typename SH>
+inline double zmarch_cost(const SH* s, int n, int variant, bool blocks, int resident, int lz) {
     int64_t items = 0;
+    int longest = 0;
     for (int i = 0; i < n; ++i) {
         const SampleDev& sd = s[i].dev;
-        if (sd.variant < 0) continue;
-        items += (int64_t)zmarch_rows(sd, true) * ((sd.nz + tile_lz(0) - 1) / tile_lz(0));
+        if (sd.variant != variant) continue;
+        items += (int64_t)zmarch_rows(sd, blocks) * ((sd.nz + lz - 1) / lz);
+        longest = std::max(longest, std::min(lz, sd.nz));
     }
-    return items;
+    const int64_t per_cu = (items + kZrWaves * 256 - 1) / (kZrWaves * 256);
+    const int64_t full = per_cu / resident, rest = per_cu % resident;
+    return (longest + 2) * (full * (2.2 + resident) + (rest ? 2.2 + rest : 0.0));
+}
+
+template <typename SH>
+inline int zmarch_segment(const SH* s, int n, int variant, bool blocks, int resident) {
+    constexpr int kCand[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
+    const int lo = zmarch_min_lz(s, n);
+    double best = 0;
+    int best_lz = 0;
+    for (const int lz : kCand) {
+        if (lz < lo) continue;
+        const double t = zmarch_cost(s, n, variant, blocks, resident, lz);
+        if (best_lz == 0 || t < best) {
+            best = t;
+            best_lz = lz;
+        }
+    }
+    return best_lz;
 }
 
 // Autotune cache: one line per entry "tau1 <arch> q<Q> p<P> n<bucket> tile <t> ms <x>".

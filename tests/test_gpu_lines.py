@@ -1,6 +1,6 @@
 """The row kernel (kernel 0: one node per lane, windows of at most 62 nodes,
 rows of 64 nodes without neighbour lanes) at the edges of its windows and
-z-segments, against the FP64 oracle, and against the z-march's bits."""
+z-segments, against the FP64 oracle."""
 import numpy as np
 import pytest
 
@@ -41,19 +41,3 @@ def test_window_edges_reduced(prec, dims):
     assert err["u_rel_l2"] <= 8.0 * eps, err
     assert err["drho_abs"] <= (2.0 * eps + 16.0 * 2.0 ** -24) * np.abs(u).max(), err
     sim.close()
-
-
-@pytest.mark.parametrize("q,prec", [(15, "f32"), (19, "f32"), (27, "f32"), (19, "f16"),
-                                    (19, "bf16")])
-@pytest.mark.parametrize("dims", [(16, 9, 7), (48, 7, 20), (64, 6, 9), (96, 5, 6), (128, 9, 18),
-                                  (288, 3, 4), (512, 5, 3)])
-def test_same_values_as_zmarch(q, prec, dims):
-    """Every sum is formed in the z-march's order: the values are equal."""
-    nx, ny, nz = dims
-    solid, drho, u = inputs.random_state(nx, ny, nz, seed=5 + nx)
-    print(f"[case] rows = z-march q={q} {prec} dims={dims}", flush=True)
-    a, oa = run_gpu([(solid, drho, u)], q, prec, G, 5, kernel=0)
-    b, ob = run_gpu([(solid, drho, u)], q, prec, G, 5, kernel=1)
-    assert np.array_equal(oa[0][0], ob[0][0]) and np.array_equal(oa[0][1], ob[0][1])
-    a.close()
-    b.close()
