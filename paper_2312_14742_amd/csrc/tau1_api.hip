@@ -49,6 +49,7 @@ struct Plan {
     size_t total = 0;
     int64_t ntiles = 0;
     int64_t total_blocks = 0;
+    int d2_span = 1;           // D2Q9: most steps a launch takes
     bool packed = false;       // some sample uses the packed layout
     bool pack_refused = false; // packed layout requested but no sample qualifies
     std::vector<SampleHost> s;
@@ -214,14 +215,15 @@ Plan make_plan(const tau1_desc* d, bool tables) {
         sd.words = (int32_t)((in.nx + 31) / 32);
         sd.stride = (int64_t)(align_up((size_t)sd.n * sz, kAlign) / sz);
         zmarch_tiling(sd);
-        if (d->lattice == 9) {
-            sd.variant = -1;  // the D2Q9 kernel only
-            sd.block0 = blocks;
-            blocks += (sd.n + kNodeBlock - 1) / kNodeBlock;
-        }
+        if (d->lattice == 9) sd.variant = -1;  // the D2Q9 kernel only
         maxn = std::max<int64_t>(maxn, sd.n);
     }
-    if (d->lattice != 9) blocks = lines_tiling(p.s.data(), d->n_samples, d->precision);
+    if (d->lattice == 9) {
+        p.d2_span = d2q9_steps(p.s.data(), d->n_samples);
+        blocks = d2q9_blocks(p.s.data(), d->n_samples, p.d2_span);
+    } else {
+        blocks = lines_tiling(p.s.data(), d->n_samples, d->precision);
+    }
     // packed layout: by default for the z-march precisions (FP32 and the
     // 16-bit storage modes) unless a dense-layout tile is asked for;
     // one-row-per-wave lane layouts only, and only where the z-march kernel
@@ -479,7 +481,7 @@ Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
         l.shmem = 0;
     } else if (kernel == 2) {
         l.fn = pick_d2q9(ctx->precision);
-        l.block = dim3(kNodeBlock);
+        l.block = dim3(kD2Threads);
         l.grid = dim3((unsigned)ctx->plan.total_blocks);
         l.shmem = 0;
     } else {
@@ -497,6 +499,18 @@ int launch_groups(const tau1_ctx* ctx, int kernel) {
 
 StepArgs* launch_args(tau1_ctx* ctx, int kernel, int g, int parity) {
     return kernel == 1 ? &ctx->zgroups[g].args[parity] : &ctx->args[parity];
+}
+
+// D2Q9: a launch of `steps` time steps reading buffer `parity` (at most
+// plan.d2_span; each launch moves the state to the other buffer).
+tau1_status launch_d2q9(tau1_ctx* ctx, int steps, int parity) {
+    const Launch l = step_launch(ctx, 2, 0, 0);
+    if (!l.fn) return TAU1_E_UNSUPPORTED;
+    StepArgs a = ctx->args[parity];
+    a.d2_steps = steps;
+    void* params[] = {&a};
+    HIP_TRY(hipLaunchKernel(l.fn, l.grid, l.block, params, l.shmem, ctx->stream));
+    return TAU1_OK;
 }
 
 // One time step reading buffer `parity`: every launch of the step in order.
@@ -536,8 +550,8 @@ void destroy_graph(tau1_ctx* ctx) {
     ctx->graph_kernel = ctx->graph_tile = -1;
 }
 
-// Graph of graph_chunk time steps.  The parity alternates step by step and,
-// graph_chunk being even, the graph maps the current buffer onto itself.
+// Graph of graph_chunk time steps.  The parity alternates step by step (D2Q9:
+// launch by launch) and, graph_chunk being even, the graph maps the current buffer onto itself.
 // A context with several launch groups (a batch of several z-march lane
 // layouts) either runs them as one chain -- the launches of a step one after
 // another, each with the whole GPU -- or as one chain per group, the chains
@@ -552,9 +566,11 @@ tau1_status build_graph(tau1_ctx* ctx) {
         ls.push_back(step_launch(ctx, ctx->kernel, ctx->tile, g));
         if (!ls.back().fn) return TAU1_E_UNSUPPORTED;
     }
-    auto add = [&](int g, int s, hipGraphNode_t* prev) -> tau1_status {
+    auto add = [&](int g, int s, hipGraphNode_t* prev, int d2_steps = 0) -> tau1_status {
         const Launch& l = ls[g];
-        void* params[] = {launch_args(ctx, ctx->kernel, g, (ctx->parity + s) & 1)};
+        StepArgs a = *launch_args(ctx, ctx->kernel, g, (ctx->parity + s) & 1);
+        a.d2_steps = d2_steps;
+        void* params[] = {&a};
         hipKernelNodeParams kp{};
         kp.func = l.fn;
         kp.gridDim = l.grid;
@@ -568,7 +584,19 @@ tau1_status build_graph(tau1_ctx* ctx) {
         *prev = node;
         return TAU1_OK;
     };
-    if (ctx->graph_chains || ng == 1) {
+    if (ctx->kernel == 2) {
+        // an even number of launches (the last buffer written is the one first
+        // read), their steps as even as they come
+        const int span = ctx->plan.d2_span;
+        const int n = 2 * ((ctx->graph_chunk + 2 * span - 1) / (2 * span));
+        hipGraphNode_t prev = nullptr;
+        for (int s = 0; s < n; ++s) {
+            const int steps = (int)((int64_t)ctx->graph_chunk * (s + 1) / n) -
+                              (int)((int64_t)ctx->graph_chunk * s / n);
+            const tau1_status st = add(0, s, &prev, steps);
+            if (st != TAU1_OK) return st;
+        }
+    } else if (ctx->graph_chains || ng == 1) {
         for (int g = 0; g < ng; ++g) {
             if (ls[g].grid.x == 0) continue;
             hipGraphNode_t prev = nullptr;
@@ -1086,6 +1114,7 @@ tau1_status tau1_create(const tau1_desc* desc, tau1_ctx** out) {
         a.scale_u = std::ldexp(1.0f, lsu);
         a.inv_scale_u = std::ldexp(1.0f, -lsu);
         a.xbc = desc->x_boundary;
+        a.d2_span = ctx->plan.d2_span;
         a.din = desc->x_boundary ? desc->rho_in - 1.0 : 0.0;
         a.dout = desc->x_boundary ? desc->rho_out - 1.0 : 0.0;
         a.uw[0] = desc->wall_u[0];
@@ -1175,6 +1204,14 @@ tau1_status tau1_step(tau1_ctx* ctx, int64_t nsteps) {
             nsteps -= ctx->graph_chunk;
             ctx->steps_done += ctx->graph_chunk;
         }
+    }
+    while (nsteps > 0 && ctx->kernel == 2) {
+        const int k = (int)std::min<int64_t>(nsteps, ctx->plan.d2_span);
+        st = launch_d2q9(ctx, k, ctx->parity);
+        if (st != TAU1_OK) return st;
+        ctx->parity ^= 1;
+        nsteps -= k;
+        ctx->steps_done += k;
     }
     while (nsteps > 0) {
         st = launch_one(ctx, ctx->kernel, ctx->tile, ctx->parity);

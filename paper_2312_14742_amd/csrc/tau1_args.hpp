@@ -23,6 +23,7 @@ struct StepArgs {
     // D2Q9 boundaries: Zou-He pressure columns at x = 0 and nx - 1 (xbc = 1)
     // with densities 1 + din, 1 + dout; velocity of the moving walls
     int32_t xbc;
+    int32_t d2_steps, d2_span;  // D2Q9: steps of this launch, the most a launch takes
     int32_t pad2;
     double din, dout;
     double uw[2];
