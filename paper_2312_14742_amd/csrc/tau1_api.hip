@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -18,6 +19,7 @@
 #include "tau1_kernels.hpp"
 #include "tau1_zmarch.hpp"
 #include "tau1_lines.hpp"
+#include "tau1_readback.hpp"
 #include "tau1_service.hpp"
 
 using namespace tau1;
@@ -403,6 +405,13 @@ struct tau1_ctx {
     std::string cache;
     hipError_t last_hip = hipSuccess;
     double* scratch = nullptr;  // this context's device's copy of `scratch`
+    hipEvent_t read_ev[kReadSlots] = {};  // readback slots written
+    tau1_ctx() { ReadPool::get().add_context(); }
+    ~tau1_ctx() {
+        for (auto& ev : read_ev)
+            if (ev) (void)hipEventDestroy(ev);
+        ReadPool::get().drop_context();
+    }
 };
 
 namespace {
@@ -445,15 +454,22 @@ int group_mode(const tau1_ctx::ZGroup& g) {
     return mode == 3 && !g.packed ? 1 : mode;
 }
 
-// Workgroups of group g's z-march kernel that a CU holds.
+// Workgroups of group g's z-march kernel that a CU holds (a property of the
+// compiled kernel: asked once per kernel and process).
 int group_resident(const tau1_ctx* ctx, const tau1_ctx::ZGroup& g) {
-    int n = 0;
-    const void* fn = pick_zmarch(ctx->lattice, ctx->precision, g.variant, group_mode(g));
+    static std::atomic<int8_t> known[3][4][kNumVariants][4];
+    const int mode = group_mode(g);
+    auto& k = known[ctx->lattice == 15 ? 0 : ctx->lattice == 19 ? 1 : 2][ctx->precision][g.variant][mode];
+    int n = k.load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    const void* fn = pick_zmarch(ctx->lattice, ctx->precision, g.variant, mode);
     if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kZrThreads, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 2;
     }
-    return std::clamp(n, 1, 8);
+    n = std::clamp(n, 1, 8);
+    k.store((int8_t)n, std::memory_order_relaxed);
+    return n;
 }
 
 // Launch geometry of one step kernel: z-march group g (kernel 1), the row
@@ -774,35 +790,58 @@ tau1_status upload_sample(tau1_ctx* ctx, int s, const tau1_sample& in) {
     return TAU1_E_INVALID;
 }
 
+// Reads one sample back (tau1_readback.hpp): up to kReadSlots chunks are being
+// written by the GPU or copied out at a time.
 template <int P>
 tau1_status export_sample_t(tau1_ctx* ctx, int s, double* drho, double* u, int* nbad,
                             bool phys_rho) {
-    const SampleDev& sd = ctx->plan.s[s].dev;
-    uint8_t* stage = ctx->base + ctx->plan.stage_off;
-    int* bad = reinterpret_cast<int*>(ctx->base + ctx->plan.partial_off +
-                                      sizeof(double) * (kReduceBlocks * 4 + 4));
-    HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int), ctx->stream));
-    const int64_t n = sd.n;
-    const int64_t chunk = std::min<int64_t>(n, kStageNodes);
-    double* out = reinterpret_cast<double*>(stage);
-    for (int64_t i0 = 0; i0 < n; i0 += chunk) {
-        const int64_t len = std::min(chunk, n - i0);
-        hipLaunchKernelGGL(k_export<P>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0,
-                           ctx->stream, ctx->args[ctx->parity], s, out, i0, len, bad,
-                           phys_rho ? 1 : 0);
-        HIP_TRY(hipGetLastError());
-        if (drho)
-            HIP_TRY(hipMemcpyAsync(drho + i0, out, sizeof(double) * len, hipMemcpyDeviceToHost,
-                                   ctx->stream));
-        if (u)
-            for (int a = 0; a < 3; ++a)
-                HIP_TRY(hipMemcpyAsync(u + (int64_t)a * n + i0, out + (1 + a) * len,
-                                       sizeof(double) * len, hipMemcpyDeviceToHost,
-                                       ctx->stream));
-        HIP_TRY(hipStreamSynchronize(ctx->stream));
+    const int64_t n = ctx->plan.s[s].dev.n;
+    double* dst[4];
+    int arrays = 0;
+    if (drho) dst[arrays++] = drho;
+    for (int a = 0; u && a < 3; ++a) dst[arrays++] = u + (int64_t)a * n;
+    const int64_t chunks = (n + kReadNodes - 1) / kReadNodes;
+    const ReadBlock block((int)std::min<int64_t>(chunks, kReadSlots),
+                          (size_t)std::min(n, kReadNodes) * arrays);
+    if (!block.b.p) return TAU1_E_NOMEM;
+    for (auto& e : ctx->read_ev)
+        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    double* bad = block.tail();
+    *bad = 0.0;
+    hipError_t err = hipSuccess;
+    {
+        SlotCopy out(block, n, arrays, dst);
+        int64_t launched = 0;
+        for (int64_t c = 0; c < chunks && err == hipSuccess; ++c) {
+            while (launched < chunks && launched < c + kReadSlots && err == hipSuccess) {
+                // a slot still being copied out is waited for only by the chunk
+                // that is next in turn
+                const int64_t before = launched - kReadSlots;
+                if (before >= 0 && launched > c && !out.left(before)) break;
+                if (before >= 0) out.wait(before);
+                const int64_t i0 = launched * kReadNodes, len = std::min(kReadNodes, n - i0);
+                double* d = block.slot((int)(launched % kReadSlots));
+                hipLaunchKernelGGL(k_export<P>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0,
+                                   ctx->stream, ctx->args[ctx->parity], s, drho ? d : nullptr,
+                                   u ? d + (drho ? len : 0) : nullptr, i0, len, bad,
+                                   phys_rho ? 1 : 0);
+                err = hipGetLastError();
+                if (err == hipSuccess)
+                    err = hipEventRecord(ctx->read_ev[launched % kReadSlots], ctx->stream);
+                ++launched;
+            }
+            if (err == hipSuccess) err = hipEventSynchronize(ctx->read_ev[c % kReadSlots]);
+            if (err == hipSuccess) out.ready(c);
+        }
+        // the last chunks leave their slots before the workers end
+        for (int64_t c = std::max<int64_t>(0, chunks - kReadSlots); c < chunks && err == hipSuccess; ++c)
+            out.wait(c);
     }
-    HIP_TRY(hipMemcpyAsync(nbad, bad, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    if (err != hipSuccess) {
+        (void)hipStreamSynchronize(ctx->stream);  // nothing writes the block any more
+        return fail_hip(ctx, err);
+    }
+    *nbad = *bad != 0.0;
     return TAU1_OK;
 }
 
@@ -843,15 +882,17 @@ tau1_status reduce_launch(tau1_ctx* ctx, int s, int axis, double* partial, doubl
     return TAU1_E_INVALID;
 }
 
-// tau1_permeability's reduction: partials and results in the workspace.
+// tau1_permeability's reduction: partials in the workspace, the results
+// written straight to pinned host memory.
 tau1_status reduce_ws(tau1_ctx* ctx, int s, int axis, double out[4]) {
     double* partial = reinterpret_cast<double*>(ctx->base + ctx->plan.partial_off);
-    double* res = partial + kReduceBlocks * 4;
-    const tau1_status st = reduce_launch(ctx, s, axis, partial, res);
-    if (st != TAU1_OK) return st;
-    HIP_TRY(hipMemcpyAsync(out, res, sizeof(double) * 4, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    return TAU1_OK;
+    const ReadBlock block;
+    if (!block.b.p) return TAU1_E_NOMEM;
+    tau1_status st = reduce_launch(ctx, s, axis, partial, block.tail());
+    const hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (st == TAU1_OK && e != hipSuccess) st = fail_hip(ctx, e);
+    if (st == TAU1_OK) std::memcpy(out, block.tail(), 4 * sizeof(double));
+    return st;
 }
 
 // Selects the tile of every lane layout (`tile`, or per_variant[v] where

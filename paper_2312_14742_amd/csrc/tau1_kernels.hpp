@@ -264,14 +264,14 @@ __global__ void k_upload(StepArgs a, int s, const uint8_t* __restrict__ solid,
     }
 }
 
-// State readback: nodes [i0, i0 + len) of one sample, current buffer, into
-// FP64 staging (drho | ux | uy | uz, each len values); u = v - g/2 in FP64;
-// solid nodes read 0.  With phys_rho the first array holds rho = 1 + drho
-// (formed in FP64; 1 at solid nodes) instead.  Counts non-finite fluid values
-// into *bad.
+// State readback: nodes [i0, i0 + len) of one sample, current buffer, as FP64
+// (out_d: drho; out_u: ux | uy | uz, each len values; either may be null; both
+// may lie in pinned host memory); u = v - g/2 in FP64; solid nodes read 0.
+// With phys_rho out_d holds rho = 1 + drho (formed in FP64; 1 at solid nodes)
+// instead.  *bad is set where a fluid value is not finite.
 template <int P>
-__global__ void k_export(StepArgs a, int s, double* __restrict__ out, int64_t i0,
-                         int64_t len, int* bad, int phys_rho) {
+__global__ void k_export(StepArgs a, int s, double* __restrict__ out_d, double* __restrict__ out_u,
+                         int64_t i0, int64_t len, double* bad, int phys_rho) {
     using St = Storage<P>;
     using S = typename St::S;
     using T = typename St::T;
@@ -291,13 +291,14 @@ __global__ void k_export(StepArgs a, int s, double* __restrict__ out, int64_t i0
         ux = (double)St::load(p + sd.stride, e, inv_scale_u<P>(a)) - a.gh[0];
         uy = (double)St::load(p + 2 * sd.stride, e, inv_scale_u<P>(a)) - a.gh[1];
         uz = (double)St::load(p + 3 * sd.stride, e, inv_scale_u<P>(a)) - a.gh[2];
-        if (!isfinite(d) || !isfinite(ux) || !isfinite(uy) || !isfinite(uz))
-            atomicAdd(bad, 1);
+        if (!isfinite(d) || !isfinite(ux) || !isfinite(uy) || !isfinite(uz)) *bad = 1.0;
     }
-    out[t] = phys_rho ? 1.0 + d : d;
-    out[len + t] = ux;
-    out[2 * len + t] = uy;
-    out[3 * len + t] = uz;
+    if (out_d) out_d[t] = phys_rho ? 1.0 + d : d;
+    if (out_u) {
+        out_u[t] = ux;
+        out_u[len + t] = uy;
+        out_u[2 * len + t] = uz;
+    }
 }
 
 // ---------------------------------------------------------------------------
