@@ -606,8 +606,10 @@ __device__ __forceinline__ void chunk_voffs(const ZrItem<P, G, C, K>& it, const 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(t.hi[c], __builtin_amdgcn_mbcnt_lo(t.lo[c], 0u));
-        const uint64_t bits = ((uint64_t)t.hi[c] << 32) | t.lo[c];
-        vo[c] = ((bits >> it.lane) & 1u) ? (int)((t.rank[c] + below) * CB) : kOob;
+        // the bitmap is the lane mask of the select
+        const bool stored = __builtin_amdgcn_inverse_ballot_w64(((uint64_t)t.hi[c] << 32) | t.lo[c]);
+        const int at = (int)((t.rank[c] + below) * CB);
+        vo[c] = stored ? at : kOob;
     }
 }
 
@@ -894,10 +896,8 @@ __device__ __forceinline__ void zr_step(const ZrItem<P, G, C, K>& it, int zs, Pl
     // shared rows: the next plane's own row, requested as soon as this
     // plane's own row has been pushed (its registers are free then; any
     // earlier and they would not fit), so its loads land during the rest of
-    // the step.  Only where the instance has the registers for it at its
-    // occupancy (EARLY_OK); D3Q27's larger sums keep the request at the end
-    // of the step.
-    constexpr bool EARLY = Q < 27 && EARLY_OK;
+    // the step, where the instance has the registers for it (zr_early).
+    constexpr bool EARLY = EARLY_OK;
     if constexpr (EARLY) {
         if constexpr (PK) {
             chunk_voffs(it, tn_own, vn);
@@ -1121,38 +1121,39 @@ __device__ __forceinline__ void zr_item(const StepArgs& a, const SampleDev* sd, 
     }
 }
 
-// The packed shared-row schedule (mode 3) of FP32 D3Q15 and D3Q19, per lane
-// layout: the waves per SIMD its instance is built for -- the occupancy its
-// registers and row slots give without the early request of the next
-// plane's own row -- and whether it makes that request, which it does
-// wherever the extra registers fit that occupancy without spilling (not at
-// nx = 256: 4 waves and 128 registers leave no room).  +4 % on the 64-sample
-// batch against the request for six or more nodes per lane only.  The other
-// schedules, storage formats and lattices, where the same request would cost
-// occupancy or spill in some layouts, keep that rule.  (The multi-row
-// layouts have no shared-row schedule: 0 and false.)
-constexpr int kShareWaves[kNumVariants] = {5, 5, 4, 4, 3, 2, 2, 0, 5, 3, 3, 2, 0, 0, 0};
-constexpr bool kShareEarly[kNumVariants] = {true,  true, true,  false, true,  true,  true, false,
-                                            true,  true, true,  true,  false, false, false};
+// The shared-row schedules (modes 1 and 3), per lane layout: the waves per
+// SIMD an instance is built for, the most that its registers allow with at
+// most a few spilled.  Without the target the compiler takes 130-135 registers
+// for four nodes per lane where 128 give a fourth wave.  (The multi-row layouts
+// have no shared-row schedule: 0.)  Measured us a step on the 256^3 packed
+// lattice, at the compiler's own choice and here: FP16 119 -> 83, BF16 115 ->
+// 80, D3Q27 142 -> 116, D3Q27 FP16 145 -> 104; FP32 160^3 47.3 -> 42.8, 224^3
+// 88 -> 82.
+constexpr int kShareWaves[kNumVariants] = {5, 5, 4, 4, 3, 2, 2, 0, 5, 4, 4, 2, 0, 0, 0};
 
-constexpr bool zr_tabled(int q, int p, int mode) { return mode == 3 && p == kF32 && q < 27; }
-
-// Whether instance (Q, P, V, MODE) requests the next plane's own row early.
+// Whether instance (Q, P, V, MODE) requests the next plane's own row early:
+// every shared-row one (256^3 packed FP32 102 -> 95.5 us a step, 320^3 FP16
+// 232 -> 206, 128^3 dense 23.9 -> 21.9), but for those where the request spills
+// too many registers at the layout's waves (FP32 with four or five nodes in one
+// chunk on D3Q27, 256^3 116 against 119, and with four and idle lanes on D3Q15,
+// 224^3 75.5 against 79.4).
 constexpr bool zr_early(int q, int p, int v, int mode) {
-    return zr_tabled(q, p, mode) ? kShareEarly[v] : kVariants[v].c * kVariants[v].k >= 6;
+    const ZrVariant& l = kVariants[v];
+    if (!zr_share(l.g, mode)) return false;
+    const bool spills = l.c == 1 && ((q == 27 && (l.k == 4 || l.k == 5)) ||
+                                     (q == 15 && l.k == 4 && l.l < 64));
+    return p != kF32 || !spills;
 }
 
-// Occupancy target of an instance: the tabled schedules at their layout's
-// kShareWaves; the other shared-row schedules (one row per wave) and modes 1
-// and 3 on the multi-row layouts at two waves per SIMD or more (at most 256
-// registers per lane; the row slots of two workgroups fill a CU's LDS at the
-// longest rows); the other instances at one or more.  Modes 1/3 and 2 are the
-// same rolling-prefetch schedule on a multi-row layout, so the tile picks the
-// occupancy there.
+// Occupancy target of an instance: the shared-row schedules (one row per wave)
+// at their layout's kShareWaves; modes 1 and 3 on the multi-row layouts at two
+// waves per SIMD or more; the other instances at one or more.  Modes 1/3 and 2
+// are the same rolling-prefetch schedule on a multi-row layout, so the tile
+// picks the occupancy there.
 constexpr int zr_waves_per_simd(int q, int p, int v, int mode) {
     const int g = kVariants[v].g;
-    if (zr_share(g, mode) && zr_tabled(q, p, mode)) return kShareWaves[v];
-    return (zr_share(g, mode) || (g != 1 && (mode == 1 || mode == 3))) ? 2 : 1;
+    if (zr_share(g, mode)) return kShareWaves[v];
+    return g != 1 && (mode == 1 || mode == 3) ? 2 : 1;
 }
 
 // Work item (4 x int32): sample, row group, z-segment start, z-segment end.
@@ -1224,9 +1225,9 @@ __device__ __forceinline__ void zr_rows_item(const StepArgs& a, int v, int s, in
         constexpr ZrVariant L = kVariants[V];
         if constexpr (zr_rows_layout(L)) {
             if (v == V) {
-                // every layout requests the next plane's own row early: all
+                // D3Q15 and D3Q19 request the next plane's own row early: all
                 // run at two waves per SIMD here (+5 % on the 64-sample batch)
-                zr_item<Q, P, 1, 1, L.k, L.l, MODE, true>(a, a.samples + s, rg, z0, z1,
+                zr_item<Q, P, 1, 1, L.k, L.l, MODE, (Q < 27)>(a, a.samples + s, rg, z0, z1,
                                                     lds_all + wave * 4 * L.k * 64, wave, lds_all);
                 return;
             }
