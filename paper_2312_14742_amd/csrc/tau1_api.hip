@@ -481,7 +481,10 @@ Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
         const auto& grp = ctx->zgroups[g];
         l.fn = pick_chunks(ctx->lattice, ctx->precision, kVariants[grp.variant].k);
         l.block = dim3(kCkThreads);
-        l.grid = dim3((unsigned)((grp.args[0].ntiles + kCkWaves - 1) / kCkWaves));
+        // whole rounds of runs over the XCDs
+        constexpr int round = 8 * kCkRun;
+        l.grid = dim3((unsigned)(((grp.args[0].ntiles + kCkWaves - 1) / kCkWaves + round - 1) /
+                                 round * round));
         l.shmem = 0;
     } else if (kernel == 1 && ctx->zgroups[g].rows_mode >= 0) {
         const auto& grp = ctx->zgroups[g];

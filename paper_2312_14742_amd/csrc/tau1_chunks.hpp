@@ -77,18 +77,20 @@ __device__ __forceinline__ float ck_from_next(float v) {
 // list is in storage order); otherwise the edge node is read from memory.
 struct CkNb {
     bool left, right;  // lane l - 1 / l + 1 holds chunk ci - 1 / ci + 1 of this row
-    int cl, cr;        // the neighbour chunk indices (periodic in x)
 };
 
-// Source terms of the column's nodes x0 - 1 .. x0 + K (slots 0 .. K + 1); the
-// two edge slots only where a direction of the column needs them.  Every
-// lane of the wave takes part (the edge values move between lanes).  All
-// reads of a column are addressed from its record alone, so they are in
+// Source terms of the column's nodes x0 .. x0 + K - 1, and where a direction of
+// the column has c_x != 0 what the nodes on either side send into the chunk:
+// el along (+1, CY, CZ) from x0 - 1, er along (-1, CY, CZ) from x0 + K.  Every
+// lane of the wave takes part: a neighbouring lane that holds the chunk on that
+// side passes its own edge node's value (one lane move and one select per
+// side; passing the node's state took four of each and held it in registers).
+// All reads of a column are addressed from its record alone, so they are in
 // flight together; the edge reads of lanes whose neighbour lane holds the
 // edge use an out-of-range offset (no memory access) instead of a branch.
-template <int P, int K, bool EDGES>
+template <int P, int CY, int CZ, int K, bool EDGES>
 __device__ __forceinline__ void ck_column(const CkCtx& c, const ck_rec_t& rec, int ci,
-                                          const CkNb& nb, Src (&s)[K + 2]) {
+                                          const CkNb& nb, Src (&s)[K], float& el, float& er) {
     constexpr int ES = (int)sizeof(typename Storage<P>::S);
     constexpr uint32_t CB = (uint32_t)(K * ES);
     const uint32_t rank = rec.x & kRecIndex;
@@ -121,20 +123,15 @@ __device__ __forceinline__ void ck_column(const CkCtx& c, const ck_rec_t& rec, i
         }
     }
 #pragma unroll
-    for (int j = 0; j < K; ++j) s[j + 1] = make_src(v[0][j], v[1][j], v[2][j], v[3][j]);
+    for (int j = 0; j < K; ++j) s[j] = make_src(v[0][j], v[1][j], v[2][j], v[3][j]);
+    el = er = 0.0f;
     if constexpr (EDGES) {
-        // last node of the chunk before, first node of the chunk after: from
-        // the neighbouring lanes' loads of this column where they hold those
-        // chunks
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const float pv = ck_from_prev(v[a][K - 1]);
-            const float nv = ck_from_next(v[a][0]);
-            e[0][a] = nb.left ? pv : e[0][a];
-            e[1][a] = nb.right ? nv : e[1][a];
-        }
-        s[0] = make_src(e[0][0], e[0][1], e[0][2], e[0][3]);
-        s[K + 1] = make_src(e[1][0], e[1][1], e[1][2], e[1][3]);
+        const float ul = feq_m<1, CY, CZ>(make_src(e[0][0], e[0][1], e[0][2], e[0][3]));
+        const float ur = feq_m<-1, CY, CZ>(make_src(e[1][0], e[1][1], e[1][2], e[1][3]));
+        const float pv = ck_from_prev(feq_m<1, CY, CZ>(s[K - 1]));
+        const float nv = ck_from_next(feq_m<-1, CY, CZ>(s[0]));
+        el = nb.left ? pv : ul;
+        er = nb.right ? nv : ur;
     }
 }
 
@@ -142,7 +139,7 @@ __device__ __forceinline__ void ck_column(const CkCtx& c, const ck_rec_t& rec, i
 // (c_y, c_z) = (CY, CZ), in order, from source node x - c_x to node x.  The
 // multiply-adds are those of the z-march's push (add_to).
 template <int Q, int CY, int CZ, int K, int KD = 1>
-__device__ __forceinline__ void ck_pull(float (&acc)[4][K], const Src (&s)[K + 2]) {
+__device__ __forceinline__ void ck_pull(float (&acc)[4][K], const Src (&s)[K], float el, float er) {
     if constexpr (KD < Q) {
         using L = Lattice<Q>;
         constexpr int CX = L::c[KD].x;
@@ -150,14 +147,15 @@ __device__ __forceinline__ void ck_pull(float (&acc)[4][K], const Src (&s)[K + 2
             constexpr float w = (float)weight<Q>(KD);
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                const float u = feq_m<CX, CY, CZ>(s[j + 1 - CX]);
+                const int i = j - CX;
+                const float u = i < 0 ? el : i >= K ? er : feq_m<CX, CY, CZ>(s[i < 0 ? 0 : i >= K ? 0 : i]);
                 acc[0][j] = __builtin_fmaf(w, u, acc[0][j]);
                 if constexpr (CX != 0) acc[1][j] = __builtin_fmaf(CX * w, u, acc[1][j]);
                 if constexpr (CY != 0) acc[2][j] = __builtin_fmaf(CY * w, u, acc[2][j]);
                 if constexpr (CZ != 0) acc[3][j] = __builtin_fmaf(CZ * w, u, acc[3][j]);
             }
         }
-        ck_pull<Q, CY, CZ, K, KD + 1>(acc, s);
+        ck_pull<Q, CY, CZ, K, KD + 1>(acc, s, el, er);
     }
 }
 
@@ -167,9 +165,11 @@ template <int Q, int P, int CY, int CZ, int K>
 __device__ __forceinline__ void ck_source(const CkCtx& c, const ck_rec_t (&rec)[9], int ci,
                                           const CkNb& nb, float (&acc)[4][K]) {
     if constexpr (ck_has_dir<Q, CY, CZ>()) {
-        Src s[K + 2];
-        ck_column<P, K, ck_needs_edges<Q, CY, CZ>()>(c, rec[(1 - CY) * 3 + 1 - CZ], ci, nb, s);
-        ck_pull<Q, CY, CZ, K>(acc, s);
+        Src s[K];
+        float el, er;
+        ck_column<P, CY, CZ, K, ck_needs_edges<Q, CY, CZ>()>(c, rec[(1 - CY) * 3 + 1 - CZ], ci, nb, s,
+                                                           el, er);
+        ck_pull<Q, CY, CZ, K>(acc, s, el, er);
     }
 }
 
@@ -188,17 +188,30 @@ __device__ __forceinline__ void ck_solid_dirs(const uint32_t (&win)[3][3], uint3
 
 // Occupancy target by chunk length (the register need grows with it: every
 // wave keeps the loads of several neighbour columns in flight): four waves
-// per SIMD for one node, three for two, two for longer chunks.
-constexpr int ck_waves_per_simd(int k) { return k == 1 ? 4 : k == 2 ? 3 : 2; }
+// per SIMD for one node, three for two, and for three and four nodes three on
+// D3Q15 and D3Q19 (168 registers, at most two spilled; 256^3 at porosity 0.1,
+// 48.9 us a step at two waves and with whole edge states, 44.3 at three) and
+// two on D3Q27 (at three it spills 40, 61 -> 90 us); two above.
+constexpr int ck_waves_per_simd(int q, int k) {
+    return k == 1 ? 4 : k == 2 ? 3 : k <= 4 && q < 27 ? 3 : 2;
+}
 
 template <int Q, int P, int K>
 __global__ __launch_bounds__(kCkThreads)
-__attribute__((amdgpu_waves_per_eu(ck_waves_per_simd(K))))
+__attribute__((amdgpu_waves_per_eu(ck_waves_per_simd(Q, K))))
 void k_chunks(StepArgs a) {
     using St = Storage<P>;
     constexpr int ES = (int)sizeof(typename St::S);
     const int wave = threadIdx.x >> 6;
-    const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kCkWaves + wave);
+    // XCD-aware order: dispatch is round-robin over 8 XCDs; each XCD takes runs
+    // of kCkRun consecutive workgroups, so that the neighbour rows of a wave's
+    // chunks are mostly in that XCD's L2 (in dispatch order 72 % of the reads
+    // missed it), while the XCDs advance through the list together (256^3 at
+    // porosity 0.1 and 0.2, 320^3 at 0.1, us a step: dispatch order 46.2, 77.0,
+    // 99.8; one range per XCD 44.7, 78.5, 102.9; runs of 16 44.3, 76.1, 99.9)
+    const int turn = blockIdx.x / 8;
+    const int block = ((turn / kCkRun) * 8 + blockIdx.x % 8) * kCkRun + turn % kCkRun;
+    const int item = __builtin_amdgcn_readfirstlane(block * kCkWaves + wave);
     if (item >= a.ntiles) return;
     typedef int wi4 __attribute__((ext_vector_type(4)));
     typedef const __attribute__((address_space(4))) wi4 item_t;
@@ -246,8 +259,6 @@ void k_chunks(StepArgs a) {
         const int en = __builtin_amdgcn_mov_dpp(ei, 0x134, 0xf, 0xf, true);
         nb.left = lane > 0 && valid && ci > 0 && ep == ei - 1;
         nb.right = lane + 1 < t.z && ci + 1 < c.nch && en == ei + 1;
-        nb.cl = ci == 0 ? c.nch - 1 : ci - 1;
-        nb.cr = ci == c.nch - 1 ? 0 : ci + 1;
     }
 
     // solid windows of the nine neighbour rows: bit b is node x0 - 1 + b
@@ -270,13 +281,16 @@ void k_chunks(StepArgs a) {
     ck_source<Q, P, 1, 1, K>(c, rec, ci, nb, acc);
     ck_source<Q, P, -1, 1, K>(c, rec, ci, nb, acc);
     // source plane z: own row (c_y = c_z = 0), the rest population, rows y-1, y+1
-    Src own[K + 2];
-    ck_column<P, K, true>(c, rec[4], ci, nb, own);
-    ck_pull<Q, 0, 0, K>(acc, own);
+    Src own[K];
+    {
+        float el, er;
+        ck_column<P, 0, 0, K, true>(c, rec[4], ci, nb, own, el, er);
+        ck_pull<Q, 0, 0, K>(acc, own, el, er);
+    }
     {
         constexpr float w0 = (float)weight<Q>(0);
 #pragma unroll
-        for (int j = 0; j < K; ++j) acc[0][j] = __builtin_fmaf(w0, own[j + 1].a, acc[0][j]);
+        for (int j = 0; j < K; ++j) acc[0][j] = __builtin_fmaf(w0, own[j].a, acc[0][j]);
     }
     ck_source<Q, P, 1, 0, K>(c, rec, ci, nb, acc);
     ck_source<Q, P, -1, 0, K>(c, rec, ci, nb, acc);
@@ -293,7 +307,7 @@ void k_chunks(StepArgs a) {
     for (int j = 0; j < K; ++j) {
         if ((fluid & any) >> j & 1u) {
             float r[4];
-            wall_dirs<Q>(own[j + 1],
+            wall_dirs<Q>(own[j],
                          [&](int k) { return (uint32_t)__builtin_amdgcn_sbfe((int)sdir[k], j, 1); }, r);
 #pragma unroll
             for (int comp = 0; comp < 4; ++comp) acc[comp][j] += r[comp];

@@ -71,6 +71,7 @@ inline int tile_mode(int tile) { return tile / 4; }
 // row y + ny z (bits 7..31) and chunk index in the row (bits 0..6).
 constexpr int kCkWaves = 4;
 constexpr int kCkThreads = 64 * kCkWaves;
+constexpr int kCkRun = 16;  // consecutive workgroups an XCD takes in turn
 constexpr int kChunkBits = 7;
 inline bool tile_packed(int tile) { return tile_mode(tile) == 3 || tile == kChunkTile; }
 // The automatic choice: the layout's usual schedule at the z-segment length of
