@@ -1199,6 +1199,10 @@ void k_zmarch(StepArgs a) {
         typedef int wi4 __attribute__((ext_vector_type(4)));
         typedef const __attribute__((address_space(4))) wi4 item_t;
         const wi4 t = ((item_t*)a.tiles)[item];
+        // the row slots are written before a plane's one barrier: the item
+        // before is read to its end by all four waves first (its last plane's
+        // slot may be the first one written)
+        if (kShare && item != first) __syncthreads();
         zr_item<Q, P, G, C, K, NL, MODE, zr_early(Q, P, V, MODE)>(a, a.samples + t.x, t.y, t.z,
                                                                  t.w, lds_wave, wave, lds_all);
     }
@@ -1265,6 +1269,8 @@ void k_zmarch_rows(StepArgs a) {
         typedef const __attribute__((address_space(4))) wi4 item_t;
         const wi4 t = ((item_t*)a.tiles)[item];
         const int v = __builtin_amdgcn_readfirstlane(a.samples[t.x].variant);
+        // as in k_zmarch; here the slots also move with the layout's row length
+        if (item != first) __syncthreads();
         zr_rows_item<Q, P, MODE>(a, v, t.x, t.y, t.z, t.w, lds_all, wave);
     }
 }
