@@ -808,7 +808,7 @@ tau1_status export_sample_t(tau1_ctx* ctx, int s, double* drho, double* u, int* 
                           (size_t)std::min(n, kReadNodes) * arrays);
     if (!block.b.p) return TAU1_E_NOMEM;
     for (auto& e : ctx->read_ev)
-        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, kReadEvent));
     double* bad = block.tail();
     *bad = 0.0;
     hipError_t err = hipSuccess;

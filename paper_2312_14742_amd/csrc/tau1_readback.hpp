@@ -29,6 +29,13 @@ constexpr int64_t kReadNodes = int64_t(1) << 18;                 // nodes per sl
 constexpr int kReadWorkers = 8;
 constexpr size_t kBytesPerWorker = size_t(12) << 20;
 
+// What the host reads while later kernels of the stream still run has to be
+// visible to it: the blocks are coherent (with Portable alone that would be up
+// to HIP_HOST_COHERENT), and a slot's event, recorded behind the kernel that
+// writes it, releases to the system.
+constexpr unsigned kReadPinned = hipHostMallocPortable | hipHostMallocCoherent;
+constexpr unsigned kReadEvent = hipEventDisableTiming | hipEventReleaseToSystem;
+
 // Pinned blocks, shared by the contexts of the process: a call takes one that is
 // large enough for its duration (at most kReadSlots slots, 32 MiB), up to
 // kKeep idle ones are kept for the next, and the last context to go gives them
@@ -69,7 +76,7 @@ public:
         if (b.p) return b;
         b.bytes = size_t(1) << 16;
         while (b.bytes < bytes) b.bytes *= 2;
-        if (hipHostMalloc(&b.p, b.bytes, hipHostMallocPortable) != hipSuccess) {
+        if (hipHostMalloc(&b.p, b.bytes, kReadPinned) != hipSuccess) {
             (void)hipGetLastError();
             b.p = nullptr;
         }
