@@ -793,6 +793,37 @@ tau1_status upload_sample(tau1_ctx* ctx, int s, const tau1_sample& in) {
     return TAU1_E_INVALID;
 }
 
+// Reads one sample back through the workspace's staging area, a chunk of
+// kStageNodes at a time: the way where no pinned memory is to be had.
+template <int P>
+tau1_status export_staged_t(tau1_ctx* ctx, int s, double* drho, double* u, int* nbad,
+                            bool phys_rho) {
+    const int64_t n = ctx->plan.s[s].dev.n;
+    double* out = reinterpret_cast<double*>(ctx->base + ctx->plan.stage_off);
+    double* bad = reinterpret_cast<double*>(ctx->base + ctx->plan.partial_off) + kReduceBlocks * 4;
+    double flag = 0.0;
+    HIP_TRY(hipMemsetAsync(bad, 0, sizeof(double), ctx->stream));
+    const int64_t chunk = std::min<int64_t>(n, kStageNodes);
+    for (int64_t i0 = 0; i0 < n; i0 += chunk) {
+        const int64_t len = std::min(chunk, n - i0);
+        hipLaunchKernelGGL(k_export<P>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0,
+                           ctx->stream, ctx->args[ctx->parity], s, drho ? out : nullptr,
+                           u ? out + len : nullptr, i0, len, bad, phys_rho ? 1 : 0);
+        HIP_TRY(hipGetLastError());
+        if (drho)
+            HIP_TRY(hipMemcpyAsync(drho + i0, out, sizeof(double) * len, hipMemcpyDeviceToHost,
+                                   ctx->stream));
+        for (int a = 0; u && a < 3; ++a)
+            HIP_TRY(hipMemcpyAsync(u + (int64_t)a * n + i0, out + (1 + a) * len,
+                                   sizeof(double) * len, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+    }
+    HIP_TRY(hipMemcpyAsync(&flag, bad, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    *nbad = flag != 0.0;
+    return TAU1_OK;
+}
+
 // Reads one sample back (tau1_readback.hpp): up to kReadSlots chunks are being
 // written by the GPU or copied out at a time.
 template <int P>
@@ -806,7 +837,7 @@ tau1_status export_sample_t(tau1_ctx* ctx, int s, double* drho, double* u, int* 
     const int64_t chunks = (n + kReadNodes - 1) / kReadNodes;
     const ReadBlock block((int)std::min<int64_t>(chunks, kReadSlots),
                           (size_t)std::min(n, kReadNodes) * arrays);
-    if (!block.b.p) return TAU1_E_NOMEM;
+    if (!block.b.p) return export_staged_t<P>(ctx, s, drho, u, nbad, phys_rho);
     for (auto& e : ctx->read_ev)
         if (!e) HIP_TRY(hipEventCreateWithFlags(&e, kReadEvent));
     double* bad = block.tail();
@@ -886,11 +917,19 @@ tau1_status reduce_launch(tau1_ctx* ctx, int s, int axis, double* partial, doubl
 }
 
 // tau1_permeability's reduction: partials in the workspace, the results
-// written straight to pinned host memory.
+// written straight to pinned host memory, or to the workspace and copied where
+// there is none.
 tau1_status reduce_ws(tau1_ctx* ctx, int s, int axis, double out[4]) {
     double* partial = reinterpret_cast<double*>(ctx->base + ctx->plan.partial_off);
     const ReadBlock block;
-    if (!block.b.p) return TAU1_E_NOMEM;
+    if (!block.b.p) {
+        double* res = partial + kReduceBlocks * 4;
+        const tau1_status st = reduce_launch(ctx, s, axis, partial, res);
+        if (st != TAU1_OK) return st;
+        HIP_TRY(hipMemcpyAsync(out, res, sizeof(double) * 4, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+        return TAU1_OK;
+    }
     tau1_status st = reduce_launch(ctx, s, axis, partial, block.tail());
     const hipError_t e = hipStreamSynchronize(ctx->stream);
     if (st == TAU1_OK && e != hipSuccess) st = fail_hip(ctx, e);

@@ -60,6 +60,16 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *st) {
 }
 int hipMemsetAsync(void *d, int v, size_t n, void *st) { (void)st; memset(d, v, n); return OK; }
 typedef struct { unsigned x, y, z; } dim3_t;
+int __hipPushCallConfiguration(dim3_t g, dim3_t b, size_t l, void *s) {
+    (void)g; (void)b; (void)l; (void)s;
+    return OK;
+}
+int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *l, void **s) {
+    *g = *b = (dim3_t){1, 1, 1};
+    *l = 0;
+    *s = NULL;
+    return OK;
+}
 int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **a, size_t l, void *s) {
     (void)f; (void)g; (void)b; (void)a; (void)l; (void)s;
     ++fake_launches;

@@ -28,12 +28,13 @@ class Ctx:
                              tune_cache)
         n = ctypes.c_size_t(0)
         assert lib.tau1_workspace_size(ctypes.byref(d), ctypes.byref(n)) == 0
-        self.mem = np.full(n.value // 8 + 64, 7.0)
+        self.mem = np.zeros(n.value // 8 + 64)
         d.workspace = (self.mem.ctypes.data + 255) // 256 * 256
         d.workspace_bytes = n.value
         self.p = ctypes.c_void_p(None)
         self.shape = samples[0].solid.shape
-        assert lib.tau1_create(ctypes.byref(d), ctypes.byref(self.p)) == 0
+        st = lib.tau1_create(ctypes.byref(d), ctypes.byref(self.p))
+        assert st == 0, st
     def step(self, n):
         assert lib.tau1_step(self.p, n) == 0
     def read(self):

@@ -14,3 +14,26 @@ def test_block_and_events_are_visible_to_the_host(tmp_path):
         assert get("event_flags") & 0xffffffff == 0x2 | 0x80000000
         c.close()
     """)
+
+
+def test_no_pinned_memory(tmp_path):
+    """Without pinned memory the fields and the permeability come through the
+    workspace (here the staging area's own values: kernels do nothing)."""
+    run_host(tmp_path, """
+        for shape in [(8, 4, 4), (160, 128, 150)]:      # one chunk, two
+            c = Ctx([fluid(*shape)], precision="f64")
+            put("refuse_pinned", 1)
+            before = get("launches")
+            c.mem[:] = 7.0      # also the staging area (and the flag of non-finite values,
+            st, d, u = c.read() # which is cleared first)
+            assert st == 0
+            assert np.all(d == 7.0) and np.all(u == 7.0)
+            chunks = -(-d.size // (1 << 21))
+            assert get("launches") - before == chunks
+            assert lib.tau1_moments_drho(c.p, 0, None, u.ctypes.data) == 0
+            assert c.permeability() in (0, tau1.TAU1_E_NONFINITE)
+            put("refuse_pinned", 0)
+            assert c.read()[0] == 0
+            c.close()
+        assert get("pinned") > 0
+    """)
