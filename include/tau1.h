@@ -24,7 +24,13 @@
  * (for example a torch uint8 tensor); the buffer and the HIP stream are
  * borrowed and must outlive the context.  The context owns only host-side
  * metadata and its HIP graphs.  Host arrays passed in are copied during the
- * call; host output arrays are written during the call.
+ * call; host output arrays are written during the call.  Reading back
+ * (tau1_moments, tau1_moments_drho, tau1_permeability) goes through pinned host
+ * memory, at most 32 MiB for the duration of a call: two blocks at most stay
+ * with the process for the next call, and a thread of the library gives them
+ * back once the last context is gone.  Where no pinned memory is to be had the
+ * workspace serves instead.  A read of 24 MiB or more uses up to eight host
+ * threads while it lasts.
  *
  * Errors: every call returns a tau1_status; no C++ exception crosses the ABI.
  * On error, output arguments are left untouched and a failed create leaves

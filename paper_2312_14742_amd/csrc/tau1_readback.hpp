@@ -41,6 +41,10 @@ constexpr unsigned kReadEvent = hipEventDisableTiming | hipEventReleaseToSystem;
 // kKeep idle ones are kept for the next, and the last context to go gives them
 // back.  Blocks are no larger than a power of two above what was asked, since
 // pinning costs about 40 us a MiB at the first call.
+// hipHostFree waits until the whole device is idle, also for streams that have
+// nothing to do with this library, so a thread of the pool's own calls it.
+// Both calls are made in relaxed capture mode: neither touches a stream, and
+// another thread may be capturing.
 class ReadPool {
 public:
     struct Block {
@@ -56,14 +60,12 @@ public:
         ++contexts_;
     }
     void drop_context() {
-        Block idle[kKeep];
-        {
-            std::lock_guard<std::mutex> l(m_);
-            if (--contexts_ == 0)
-                for (size_t i = 0; i < kKeep; ++i) std::swap(idle[i], idle_[i]);
-        }
-        for (auto& b : idle)
-            if (b.p) (void)hipHostFree(b.p);
+        std::lock_guard<std::mutex> l(m_);
+        if (--contexts_ == 0)
+            for (auto& b : idle_) retire(b);
+    }
+    ~ReadPool() {
+        if (freer_.joinable()) freer_.join();
     }
     // A block of at least `bytes`; p is null when pinned memory cannot be had.
     Block take(size_t bytes) {
@@ -76,6 +78,7 @@ public:
         if (b.p) return b;
         b.bytes = size_t(1) << 16;
         while (b.bytes < bytes) b.bytes *= 2;
+        const RelaxedCapture relaxed;
         if (hipHostMalloc(&b.p, b.bytes, kReadPinned) != hipSuccess) {
             (void)hipGetLastError();
             b.p = nullptr;
@@ -88,14 +91,50 @@ public:
             if (contexts_ > 0)  // the larger blocks stay
                 for (auto& i : idle_)
                     if (i.bytes < b.bytes) std::swap(i, b);
+            retire(b);
         }
-        if (b.p) (void)hipHostFree(b.p);
+        if (b.p) (void)hipHostFree(b.p);  // no memory to note it down
     }
 
 private:
+    struct RelaxedCapture {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+        ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    };
+    // Leaves b to the freeing thread (m_ held); where none can be started it
+    // waits for the next call's, and where it cannot be noted down b is kept.
+    void retire(Block& b) {
+        if (!b.p) return;
+        try {
+            retired_.push_back(b);
+            b = Block{};
+            if (freeing_) return;
+            if (freer_.joinable()) freer_.join();  // it has left its loop
+            freer_ = std::thread([this] { free_retired(); });
+            freeing_ = true;
+        } catch (...) {
+        }
+    }
+    void free_retired() {
+        const RelaxedCapture relaxed;
+        std::unique_lock<std::mutex> l(m_);
+        while (!retired_.empty()) {
+            const Block b = retired_.back();
+            retired_.pop_back();
+            l.unlock();
+            (void)hipHostFree(b.p);
+            l.lock();
+        }
+        freeing_ = false;
+    }
+
     static constexpr size_t kKeep = 2;
     std::mutex m_;
     Block idle_[kKeep];
+    std::vector<Block> retired_;
+    std::thread freer_;
+    bool freeing_ = false;
     int contexts_ = 0;
 };
 

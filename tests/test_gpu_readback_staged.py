@@ -5,6 +5,7 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,31 @@ def test_staged_readback_has_the_same_bits(tmp_path):
                    input="int refused;\n" + SHIM, text=True, check=True)
     print("[case] readback without pinned memory", flush=True)
     assert run(shim) == run("")
+
+
+def test_last_context_goes_without_waiting_for_other_streams():
+    """Giving the pinned blocks back waits for the whole device: tau1_destroy
+    must not, nor may it hold up the contexts that follow."""
+    import torch
+    from paper_2312_14742_amd import tau1
+    from test_gpu_readback import state
+    solid, drho, u = state(64, 64, 40, seed=5)
+    a = torch.randn(8192, 8192, device="cuda:0")
+    side = torch.cuda.Stream()
+    torch.matmul(a, a)
+    torch.cuda.synchronize()
+    print("[case] destroy beside a busy stream", flush=True)
+    sim = tau1.Sim([tau1.Sample(solid, drho, u)], precision="f64")
+    sim.moments(0)
+    done = torch.cuda.Event()
+    with torch.cuda.stream(side):
+        for _ in range(40):
+            b = torch.matmul(a, a)
+        done.record(side)
+    sim.close()
+    assert not done.query()
+    with tau1.Sim([tau1.Sample(solid, drho, u)], precision="f64") as nxt:
+        d, v = nxt.moments(0)
+        assert np.array_equal(d, drho) and np.array_equal(v, u)
+    torch.cuda.synchronize()
+    del b

@@ -37,3 +37,23 @@ def test_no_pinned_memory(tmp_path):
             c.close()
         assert get("pinned") > 0
     """)
+
+
+def test_pinned_blocks_go_back_without_a_wait_of_the_caller(tmp_path):
+    """hipHostFree waits for every stream of the device: neither the last
+    context's end nor a read that finds the pool full calls it on the caller's
+    thread, and every block is given back."""
+    run_host(tmp_path, """
+        import threading, time
+        for rounds in range(3):
+            cs = [Ctx([fluid(16, 16, 40 + 8 * i)]) for i in range(4)]
+            ts = [threading.Thread(target=lambda c=c: [c.read() for _ in range(20)]) for c in cs]
+            for t in ts: t.start()
+            for t in ts: t.join()
+            for c in cs: c.close()
+            deadline = time.time() + 20
+            while get("freed") != get("pinned") and time.time() < deadline:
+                time.sleep(0.01)
+            assert get("pinned") > 0 and get("freed") == get("pinned")
+        assert get("freed_here") == 0
+    """)
