@@ -793,6 +793,19 @@ tau1_status upload_sample(tau1_ctx* ctx, int s, const tau1_sample& in) {
     return TAU1_E_INVALID;
 }
 
+// A read ends with a wait, which a stream under capture refuses; what the read
+// launches before would stay in the capture, and a replay would write to a
+// pinned block that is another call's by then.  Such a read fails first.
+tau1_status refuse_capture(tau1_ctx* ctx) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return TAU1_OK;
+    }
+    return cs == hipStreamCaptureStatusNone ? TAU1_OK
+                                            : fail_hip(ctx, hipErrorStreamCaptureUnsupported);
+}
+
 // Reads one sample back through the workspace's staging area, a chunk of
 // kStageNodes at a time: the way where no pinned memory is to be had.
 template <int P>
@@ -1322,6 +1335,8 @@ tau1_status moments_impl(tau1_ctx* ctx, int32_t sample, double* r, double* u, bo
     tau1_status st = check_usable(ctx);
     if (st != TAU1_OK) return st;
     if (sample < 0 || sample >= ctx->nsamples) return TAU1_E_INVALID;
+    st = refuse_capture(ctx);
+    if (st != TAU1_OK) return st;
     int nbad = 0;
     switch (ctx->precision) {
         case kF64: st = export_sample_t<kF64>(ctx, sample, r, u, &nbad, phys_rho); break;
@@ -1351,6 +1366,8 @@ tau1_status tau1_permeability(tau1_ctx* ctx, int32_t sample, int32_t axis, doubl
     if (st != TAU1_OK) return st;
     if (sample < 0 || sample >= ctx->nsamples || axis < 0 || axis > 2) return TAU1_E_INVALID;
     if (k && ctx->g[axis] == 0.0) return TAU1_E_INVALID;
+    st = refuse_capture(ctx);
+    if (st != TAU1_OK) return st;
     double res[4] = {0, 0, 0, 0};
     st = reduce_ws(ctx, sample, axis, res);
     if (st != TAU1_OK) return st;

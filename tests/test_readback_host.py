@@ -57,3 +57,20 @@ def test_pinned_blocks_go_back_without_a_wait_of_the_caller(tmp_path):
             assert get("pinned") > 0 and get("freed") == get("pinned")
         assert get("freed_here") == 0
     """)
+
+
+def test_reads_under_capture_launch_nothing(tmp_path):
+    """A read fails under capture (its wait is refused there); its kernels, which
+    write to a pinned block of the pool, must not end up in the captured graph."""
+    run_host(tmp_path, """
+        for call in ("read", "permeability"):
+            c = Ctx([fluid(8, 4, 4)])
+            put("capturing", 1)
+            before = get("launches")
+            st = getattr(c, call)()
+            st = st[0] if isinstance(st, tuple) else st
+            assert st == tau1.TAU1_E_HIP
+            assert get("launches") == before
+            put("capturing", 0)
+            c.close()
+    """)
