@@ -201,7 +201,9 @@ tau1_status tau1_workspace_size(const tau1_desc *desc, size_t *bytes);
  * 2.1.3: a bit mask, the wall-node lists for bounce-back, the packed chunk
  * table) and uploads the initial rho - 1 and u into the workspace (both
  * copies).  Host arrays are read during the call only.  Synchronous on the
- * stream.  TAU1_E_INVALID for a bad descriptor or initial field (non-finite,
+ * stream; the stream's device has to be the current one during this call (and
+ * tau1_autotune).
+ * TAU1_E_INVALID for a bad descriptor or initial field (non-finite,
  * rho <= 0, or outside the F16 range), TAU1_E_WORKSPACE for a missing,
  * misaligned or too small workspace, TAU1_E_UNSUPPORTED for a valid request
  * this build does not serve.  On error *out is NULL and nothing is owned. */

@@ -851,8 +851,6 @@ tau1_status export_sample_t(tau1_ctx* ctx, int s, double* drho, double* u, int* 
     const ReadBlock block((int)std::min<int64_t>(chunks, kReadSlots),
                           (size_t)std::min(n, kReadNodes) * arrays);
     if (!block.b.p) return export_staged_t<P>(ctx, s, drho, u, nbad, phys_rho);
-    for (auto& e : ctx->read_ev)
-        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, kReadEvent));
     double* bad = block.tail();
     *bad = 0.0;
     hipError_t err = hipSuccess;
@@ -1241,6 +1239,16 @@ tau1_status tau1_create(const tau1_desc* desc, tau1_ctx** out) {
         ctx->n_fluid += nf;
         ctx->n_nodes += rows * s.nx;
     }
+    // an event belongs to the device that is current when it is made: the
+    // readback's are made here, like all that depends on it, and a later call
+    // may find another device current
+    for (auto& e : ctx->read_ev)
+        if (hipEventCreateWithFlags(&e, kReadEvent) != hipSuccess) {
+            e = nullptr;
+            (void)hipGetLastError();
+            delete ctx;
+            return TAU1_E_HIP;
+        }
     // descriptors
     std::vector<SampleDev> sdev(ctx->nsamples);
     for (int i = 0; i < ctx->nsamples; ++i) sdev[i] = ctx->plan.s[i].dev;

@@ -74,3 +74,16 @@ def test_reads_under_capture_launch_nothing(tmp_path):
             put("capturing", 0)
             c.close()
     """)
+
+
+def test_events_are_made_with_the_context(tmp_path):
+    """The readback's events are made by tau1_create, where the context's device
+    is the current one, and not by the first read."""
+    run_host(tmp_path, """
+        c = Ctx([fluid(8, 4, 4)])
+        made = get("events")
+        assert made > 0
+        assert c.read()[0] == 0
+        assert get("events") == made
+        c.close()
+    """)
