@@ -72,8 +72,8 @@ typedef struct tau1_ctx tau1_ctx; /* opaque, owned by the library */
 
 /* D2Q9 is the two-dimensional lattice of the paper's validation runs
  * (pressure-driven Poiseuille flow, lid-driven cavity): samples have nz = 1,
- * F64 or F32 only, one thread per node; its node types and boundaries are
- * described at tau1_desc. */
+ * F64 or F32 only, up to ten steps per launch; its node types and boundaries
+ * are described at tau1_desc. */
 typedef enum { TAU1_D2Q9 = 9, TAU1_D3Q15 = 15, TAU1_D3Q19 = 19, TAU1_D3Q27 = 27 } tau1_lattice;
 
 /* Arithmetic and storage of (rho - 1, u):
@@ -188,7 +188,8 @@ typedef struct {
                                 the row kernel                              */
     int32_t launches_per_step; /* kernel launches one step takes (one per
                                 z-march lane layout, or one for all the
-                                one-chunk rows with batch_graph 3)          */
+                                one-chunk rows with batch_graph 3; 1 on D2Q9,
+                                where a launch may hold up to ten steps)    */
 } tau1_info;
 
 /* Bytes of device workspace the descriptor needs: two copies of the state
@@ -210,7 +211,9 @@ tau1_status tau1_workspace_size(const tau1_desc *desc, size_t *bytes);
 tau1_status tau1_create(const tau1_desc *desc, tau1_ctx **out);
 
 /* Enqueues nsteps >= 0 time steps on the stream and returns without waiting
- * (graph replays of graph_chunk steps, then single launches).  One step
+ * (graph replays of graph_chunk steps, then single launches).  An even nsteps
+ * leaves the state in the buffer it was in, so a captured sequence of fewer than
+ * graph_chunk steps can be replayed.  One step
  * advances every fluid node of every sample by the Tau1 update: the
  * equilibria of Eq. (3) at the sources x - c_k arrive at x (Eq. (8)), their
  * zeroth and first moments are the new density and momentum (Eqs. (9)-(10),

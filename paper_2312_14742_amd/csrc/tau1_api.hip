@@ -520,8 +520,21 @@ StepArgs* launch_args(tau1_ctx* ctx, int kernel, int g, int parity) {
     return kernel == 1 ? &ctx->zgroups[g].args[parity] : &ctx->args[parity];
 }
 
-// D2Q9: a launch of `steps` time steps reading buffer `parity` (at most
-// plan.d2_span; each launch moves the state to the other buffer).
+// D2Q9: launches for `steps` time steps, at most `span` in each.  Each launch
+// moves the state to the other buffer, so their number is even where that of the
+// steps is: an even count ends on the buffer it began with, as one step per
+// launch would.  A caller's captured sequence then goes on from its own result
+// at each replay, and a cached graph, which reads one buffer, stays usable.
+int64_t d2_launches(int64_t steps, int span) {
+    const int64_t n = (steps + span - 1) / span;
+    return n + ((n ^ steps) & 1);
+}
+// Steps of launch i of n, as even as they come.
+int d2_share(int64_t steps, int64_t n, int64_t i) {
+    return (int)(steps * (i + 1) / n - steps * i / n);
+}
+
+// D2Q9: a launch of `steps` time steps reading buffer `parity`.
 tau1_status launch_d2q9(tau1_ctx* ctx, int steps, int parity) {
     const Launch l = step_launch(ctx, 2, 0, 0);
     if (!l.fn) return TAU1_E_UNSUPPORTED;
@@ -604,15 +617,10 @@ tau1_status build_graph(tau1_ctx* ctx) {
         return TAU1_OK;
     };
     if (ctx->kernel == 2) {
-        // an even number of launches (the last buffer written is the one first
-        // read), their steps as even as they come
-        const int span = ctx->plan.d2_span;
-        const int n = 2 * ((ctx->graph_chunk + 2 * span - 1) / (2 * span));
+        const int n = (int)d2_launches(ctx->graph_chunk, ctx->plan.d2_span);
         hipGraphNode_t prev = nullptr;
         for (int s = 0; s < n; ++s) {
-            const int steps = (int)((int64_t)ctx->graph_chunk * (s + 1) / n) -
-                              (int)((int64_t)ctx->graph_chunk * s / n);
-            const tau1_status st = add(0, s, &prev, steps);
+            const tau1_status st = add(0, s, &prev, d2_share(ctx->graph_chunk, n, s));
             if (st != TAU1_OK) return st;
         }
     } else if (ctx->graph_chains || ng == 1) {
@@ -1309,13 +1317,16 @@ tau1_status tau1_step(tau1_ctx* ctx, int64_t nsteps) {
             ctx->steps_done += ctx->graph_chunk;
         }
     }
-    while (nsteps > 0 && ctx->kernel == 2) {
-        const int k = (int)std::min<int64_t>(nsteps, ctx->plan.d2_span);
-        st = launch_d2q9(ctx, k, ctx->parity);
-        if (st != TAU1_OK) return st;
-        ctx->parity ^= 1;
-        nsteps -= k;
-        ctx->steps_done += k;
+    if (nsteps > 0 && ctx->kernel == 2) {
+        const int64_t n = d2_launches(nsteps, ctx->plan.d2_span), left = nsteps;
+        for (int64_t i = 0; i < n; ++i) {
+            const int k = d2_share(left, n, i);
+            st = launch_d2q9(ctx, k, ctx->parity);
+            if (st != TAU1_OK) return st;
+            ctx->parity ^= 1;
+            nsteps -= k;
+            ctx->steps_done += k;
+        }
     }
     while (nsteps > 0) {
         st = launch_one(ctx, ctx->kernel, ctx->tile, ctx->parity);
