@@ -3,30 +3,38 @@
 //
 // A wave owns a window of at most 62 consecutive x-nodes of one row (plus the
 // node on either side in the first and last lane, periodic in x; rows of 64
-// nodes need no such lanes) and marches along z over a segment of planes.  Per
-// source plane it reads the window of rows y - 1, y, y + 1 with one coalesced
-// load per row and array, requested one plane ahead, forms the sources and
-// sends each group of directions (tau1_sums.hpp) to the planes z - 1, z, z + 1;
-// values for x +- 1 move one lane by DPP.
+// nodes need no such lanes) and marches along z over a segment of planes,
+// holding the sources of rows y - 1, y, y + 1 in planes z - 1, z, z + 1.  Per
+// plane it reads the three rows of the plane two ahead with one coalesced load
+// per row and array; what arrives from x +- 1 is formed in the source's lane and
+// moves one lane by DPP.
 //
-// Solid links need no vector work: with one node per lane, the solid bits of a
-// row window are a lane mask.  They are read with scalar loads from the
-// extended mask, shifted on the scalar unit, and select each bounced-back
-// value with one v_cndmask; a window without a wall node skips them all.
+// Arithmetic: each node adds what arrives direction by direction, in the
+// lattice's order, every operation rounded by itself and one division a node.
+// This is the plain evaluation of Eqs. (3) and (9)-(11) that FP64 mode is the
+// reference by: with g = 0 its bits are the oracle's, and FP32 and 16-bit
+// storage are the same operations in FP32.
 //
-// What bounds it: vector issue (about 210 instructions a node and plane in
-// FP32 D3Q19, wall returns included, beside 140 scalar ones) at the share of
-// lanes that a row fills, and on small lattices the chain of planes of one
-// segment, so segments are cut until the waves fill the card (lines_tiling).
-// Measured per step against a pull kernel with one thread per node, which
-// read 76 values and formed 64-bit addresses and zero-component products for
-// each: 32^3 FP64 8.4 -> 3.9 us, porous 128^3 FP64 135 -> 36 us, porous 150 x
-// 110 x 90 FP32 56 -> 17.5 us.
+// Solid links need no vector work to be found: with one node per lane, the
+// solid bits of a row window are a lane mask.  They are read with scalar loads
+// from the extended mask, rotated on the scalar unit, and select each
+// bounced-back value with one v_cndmask; a pair of opposite directions without
+// a link in the window skips its own values.
+//
+// What bounds it: vector issue (about 500 instructions a node and plane on
+// D3Q19, wall returns included) at the share of lanes that a row fills, and on
+// small lattices the three planes in a row that a segment's first result needs,
+// so segments are cut until the waves fill the card (lines_tiling).  Measured
+// per step against a pull kernel with one thread per node, which read 76 values
+// and formed 64-bit addresses and zero-component products for each: 32^3 FP64
+// 8.4 -> 4.6 us, porous 128^3 FP64 135 -> 53 us, porous 150 x 110 x 90 FP32 56
+// -> 23 us.  (Sums by groups of directions with fused multiply-adds took 3.9,
+// 36 and 17.5 us, at about twice the FP64 error.)
 #pragma once
 
 #include <algorithm>
 
-#include "tau1_sums.hpp"
+#include "tau1_args.hpp"
 
 namespace tau1 {
 
@@ -53,26 +61,20 @@ __device__ __forceinline__ double ln_move64(double v) {
 __device__ __forceinline__ double ln_prev(double v) { return ln_move64<0x13C>(v); }
 __device__ __forceinline__ double ln_next(double v) { return ln_move64<0x134>(v); }
 
-// The sums of one node in one destination plane, and the stored state of one
-// node.
-template <typename T>
-struct LnSum {
-    T t, s, x, y;
-};
+// The stored state of one node, and what its equilibria are formed from
+// (h = 1.5 v.v).
 template <typename T>
 struct LnNode {
     T d, vx, vy, vz;
 };
-
-// Solid bits of a row window for c_x = -1, 0, +1: bit l of m[c_x + 1] is set
-// when the node at c_x from lane l's node is solid.
-struct LnMask {
-    uint64_t m[3];
+template <typename T>
+struct LnSrc {
+    T d, vx, vy, vz, h;
 };
 
-// The four words of the extended mask that hold a row window's bits.
+// The words of the extended mask that hold a row window's solid bits.
 struct LnWords {
-    uint32_t w[4];
+    uint32_t w[3];
 };
 
 // Constants of one work item (one wave); uniform but for xb and lane masks.
@@ -87,7 +89,8 @@ struct LnItem {
     int nz, z0, z1, xs;
     uint32_t xb;                // byte offset of the lane's node in its row
     uint64_t lanes;             // lanes whose node belongs to the window
-    T isr, isu, sr, su, gx, gy, gz;
+    T isr, isu, sr, su;
+    T gx, gy, gz;               // g / 2
 };
 
 // The march's position: plane to be requested next.
@@ -121,11 +124,18 @@ __device__ __forceinline__ void ln_load(const LnItem<P>& it, const char* row,
 }
 
 template <int P>
-__device__ __forceinline__ SrcT<typename Storage<P>::T> ln_src(const LnItem<P>& it,
-                                                              const LnNode<typename Storage<P>::S>& r) {
+__device__ __forceinline__ LnSrc<typename Storage<P>::T> ln_src(const LnItem<P>& it,
+                                                               const LnNode<typename Storage<P>::S>& r) {
+#pragma clang fp contract(off)
     using St = Storage<P>;
-    return make_src(St::load(&r.d, 0, it.isr), St::load(&r.vx, 0, it.isu), St::load(&r.vy, 0, it.isu),
-                    St::load(&r.vz, 0, it.isu));
+    using T = typename St::T;
+    LnSrc<T> s;
+    s.d = St::load(&r.d, 0, it.isr);
+    s.vx = St::load(&r.vx, 0, it.isu);
+    s.vy = St::load(&r.vy, 0, it.isu);
+    s.vz = St::load(&r.vz, 0, it.isu);
+    s.h = (T)1.5 * ((s.vx * s.vx + s.vy * s.vy) + s.vz * s.vz);
+    return s;
 }
 
 // Scalar loads: the mask is constant while a step runs and the row uniform.
@@ -133,75 +143,113 @@ __device__ __forceinline__ void ln_words(const char* row, LnWords& o) {
     typedef const __attribute__((address_space(4))) uint32_t word_t;
     word_t* w = (word_t*)row;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o.w[i] = w[i];
+    for (int i = 0; i < 3; ++i) o.w[i] = w[i];
 }
 
-// The lane masks of a row window whose first bit is bit xs of the words.
-__device__ __forceinline__ LnMask ln_mask(const LnWords& w, int xs) {
+// Solid lanes of a row window whose first bit is bit xs of the words.
+__device__ __forceinline__ uint64_t ln_mask(const LnWords& w, int xs) {
     const uint64_t a = ((uint64_t)w.w[1] << 32) | w.w[0];
-    const uint64_t b = ((uint64_t)w.w[3] << 32) | w.w[2];
-    const uint64_t lo = (a >> xs) | ((b << (63 - xs)) << 1);
-    const uint64_t hi = b >> xs;
-    return {{lo, (lo >> 1) | (hi << 63), (lo >> 2) | (hi << 62)}};
+    return (a >> xs) | (((uint64_t)w.w[2] << (63 - xs)) << 1);
 }
 
-template <int Q, int CY, int CZ, typename T>
-__device__ __forceinline__ void ln_group(const SrcT<T>& s, T f, T g, LnSum<T>& q, T& m) {
-    using G = Group<Q, CY, CZ>;
-    if constexpr (G::has0 || G::hasx) {
-        level_z<CZ>(s, f, g);
-        T a = 0, b = 0;
-        if constexpr (G::hasx) {
-            T fp, fm;
-            level_x(s, f, g, fp, fm);
-            a = ln_prev(fp);
-            b = ln_next(fm);
-        }
-        add_group<Q, CY, CZ>(group_sum<Q, CY, CZ>(f, a, b), G::hasx ? a - b : (T)0, q.t, q.s, q.x,
-                             q.y, m);
+// c.v of direction K at a source.
+template <int Q, int K, typename T>
+__device__ __forceinline__ T ln_cu(const LnSrc<T>& s) {
+#pragma clang fp contract(off)
+    constexpr Dir c = Lattice<Q>::c[K];
+    T cu = 0;
+    if constexpr (c.x != 0) cu = c.x > 0 ? s.vx : -s.vx;
+    if constexpr (c.y != 0) {
+        const T v = c.y > 0 ? s.vy : -s.vy;
+        cu = c.x != 0 ? cu + v : v;
     }
+    if constexpr (c.z != 0) {
+        const T v = c.z > 0 ? s.vz : -s.vz;
+        cu = c.x != 0 || c.y != 0 ? cu + v : v;
+    }
+    return cu;
 }
 
-// A source row's directions c_y = CY; ZS as in the z-march's step: 0 = a plane
-// of the segment, +1 / -1 = the plane before / after it (to one plane only).
-template <int Q, int CY, int ZS, typename T>
-__device__ __forceinline__ void ln_push(const SrcT<T>& s, LnSum<T>& pm, LnSum<T>& pc, LnSum<T>& pp,
-                                        T& m) {
-    T f, g;
-    level_y<CY>(s, f, g);
-    if constexpr (ZS == 0) ln_group<Q, CY, 0>(s, f, g, pc, m);
-    if constexpr (ZS >= 0) ln_group<Q, CY, 1>(s, f, g, pp, m);
-    if constexpr (ZS <= 0) ln_group<Q, CY, -1>(s, f, g, pm, m);
+// What a source sends in direction K: Eq. (3) minus its weight.
+template <int Q, int K, typename T>
+__device__ __forceinline__ T ln_feq(const LnSrc<T>& s) {
+#pragma clang fp contract(off)
+    const T cu = ln_cu<Q, K>(s);
+    const T p = ((T)3 * cu + ((T)4.5 * cu) * cu) - s.h;
+    return (T)weight<Q>(K) * (s.d + ((T)1 + s.d) * p);
 }
 
-// Solid bits of rows y - 1, y, y + 1 of one plane.
+// Source rows y - 1, y, y + 1 of one plane.
+template <typename T>
+struct LnPlane {
+    LnSrc<T> row[3];
+};
+
+// What arrives in direction K from the planes z - 1, z, z + 1.
+template <int Q, int K, typename T>
+__device__ __forceinline__ T ln_arrive(const LnPlane<T>& pm, const LnPlane<T>& pc,
+                                       const LnPlane<T>& pp) {
+    constexpr Dir c = Lattice<Q>::c[K];
+    const LnPlane<T>& p = c.z > 0 ? pm : c.z < 0 ? pp : pc;
+    const T f = ln_feq<Q, K>(p.row[1 - c.y]);
+    if constexpr (c.x > 0) return ln_prev(f);
+    else if constexpr (c.x < 0) return ln_next(f);
+    else return f;
+}
+
+// Adds direction K's value to a node's density and momentum.
+template <int Q, int K, typename T>
+__device__ __forceinline__ void ln_add(LnNode<T>& n, T f) {
+#pragma clang fp contract(off)
+    constexpr Dir c = Lattice<Q>::c[K];
+    n.d += f;
+    if constexpr (c.x != 0) n.vx += c.x > 0 ? f : -f;
+    if constexpr (c.y != 0) n.vy += c.y > 0 ? f : -f;
+    if constexpr (c.z != 0) n.vz += c.z > 0 ? f : -f;
+}
+
+// Solid lanes of rows y - 1, y, y + 1 of one plane.
 struct LnSolid {
-    LnMask row[3];
+    uint64_t row[3];
 };
 
-// The selection of wall_sums: direction k's value in the lanes whose neighbour
-// x + c_k is solid (sm, sc, sp: planes z - 1, z, z + 1; fluid: the window's
-// fluid nodes).
-template <int Q>
-struct LnPick {
-    const LnSolid &sm, &sc, &sp;
-    uint64_t fluid;
-    template <typename K>
-    __device__ __forceinline__ uint64_t links(K) const {
-        constexpr Dir c = Lattice<Q>::c[K::value];
-        const LnSolid& s = c.z < 0 ? sm : c.z > 0 ? sp : sc;
-        return s.row[c.y + 1].m[c.x + 1] & fluid;
-    }
-    template <typename K, typename T>
-    __device__ __forceinline__ T operator()(K k, T u) const {
-        return __builtin_amdgcn_inverse_ballot_w64(links(k)) ? u : (T)0;
-    }
-};
+// Lanes whose neighbour x + c_K is solid (sm, sc, sp: planes z - 1, z, z + 1):
+// the row's solid lanes, rotated by one for c_x, as the values move.
+template <int Q, int K>
+__device__ __forceinline__ uint64_t ln_links(const LnSolid& sm, const LnSolid& sc, const LnSolid& sp) {
+    constexpr Dir c = Lattice<Q>::c[K];
+    const LnSolid& s = c.z < 0 ? sm : c.z > 0 ? sp : sc;
+    const uint64_t m = s.row[c.y + 1];
+    return c.x < 0 ? (m << 1) | (m >> 63) : c.x > 0 ? (m >> 1) | (m << 63) : m;
+}
 
-template <int Q, int K = 1>
-__device__ __forceinline__ uint64_t ln_any_link(const LnPick<Q>& p) {
-    if constexpr (K >= Q) return 0;
-    else return p.links(std::integral_constant<int, K>{}) | ln_any_link<Q, K + 1>(p);
+// Directions K and K + 1 (opposite) of one node onwards, in order.  A source
+// x - c_K that is solid returns the node's own value in the opposite direction
+// (halfway bounce-back, Eq. (11)); the two own values share their terms, and are
+// formed only where some lane of the window needs one.
+template <int Q, int K = 1, typename T>
+__device__ __forceinline__ void ln_gather(const LnPlane<T>& pm, const LnPlane<T>& pc,
+                                          const LnPlane<T>& pp, const LnSolid& sm,
+                                          const LnSolid& sc, const LnSolid& sp, uint64_t fluid,
+                                          LnNode<T>& n) {
+#pragma clang fp contract(off)
+    if constexpr (K < Q) {
+        T a = ln_arrive<Q, K>(pm, pc, pp), b = ln_arrive<Q, K + 1>(pm, pc, pp);
+        const uint64_t la = ln_links<Q, K + 1>(sm, sc, sp) & fluid;  // x - c_K is x + c_(K + 1)
+        const uint64_t lb = ln_links<Q, K>(sm, sc, sp) & fluid;
+        if (la | lb) {
+            const LnSrc<T>& o = pc.row[1];
+            const T cu = ln_cu<Q, K>(o), rho = (T)1 + o.d;
+            const T t1 = (T)3 * cu, t2 = ((T)4.5 * cu) * cu;
+            const T fk = (T)weight<Q>(K) * (o.d + rho * ((t1 + t2) - o.h));
+            const T fo = (T)weight<Q>(K) * (o.d + rho * ((t2 - t1) - o.h));
+            a = __builtin_amdgcn_inverse_ballot_w64(la) ? fo : a;
+            b = __builtin_amdgcn_inverse_ballot_w64(lb) ? fk : b;
+        }
+        ln_add<Q, K>(n, a);
+        ln_add<Q, K + 1>(n, b);
+        ln_gather<Q, K + 2>(pm, pc, pp, sm, sc, sp, fluid, n);
+    }
 }
 
 // The three rows of a plane as requested: raw state and mask words.
@@ -220,68 +268,67 @@ __device__ __forceinline__ void ln_request(const LnItem<P>& it, const LnAt& at, 
     }
 }
 
-// One source plane zs, whose rows are in `ahead`; requests plane zs + 1's rows
-// unless it is the last.  sm, sc: solid bits of planes zs - 1 and zs; sp
-// receives those of zs + 1.
-template <int Q, int P, int ZS>
-__device__ __forceinline__ void ln_step(const LnItem<P>& it, int zs, LnSum<typename Storage<P>::T>& pm,
-                                        LnSum<typename Storage<P>::T>& pc,
-                                        LnSum<typename Storage<P>::T>& pp, const LnSolid& sm,
-                                        const LnSolid& sc, LnSolid& sp, LnRows<P>& ahead, LnAt& at,
-                                        char*& out) {
-    using St = Storage<P>;
-    using T = typename St::T;
-    using S = typename St::S;
-    const SrcT<T> m1 = ln_src(it, ahead.row[0]), o = ln_src(it, ahead.row[1]),
-                  p1 = ln_src(it, ahead.row[2]);
-    if constexpr (ZS >= 0) {
-        ln_next_plane(it, at);
-        ln_request(it, at, ahead);
-    }
-    T m = 0;
-    ln_push<Q, 0, ZS>(o, pm, pc, pp, m);
-    ln_push<Q, 1, ZS>(m1, pm, pc, pp, m);
-    ln_push<Q, -1, ZS>(p1, pm, pc, pp, m);
-    if constexpr (ZS >= 0) {
-        // the mask words have landed meanwhile
+// The rows of a requested plane, landed: sources and solid bits.
+template <int P>
+__device__ __forceinline__ void ln_take(const LnItem<P>& it, LnRows<P>& r,
+                                        LnPlane<typename Storage<P>::T>& p, LnSolid& s) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < 3; ++i) {
+        p.row[i] = ln_src(it, r.row[i]);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) asm volatile("" : "+s"(ahead.words[i].w[k]));
-            sp.row[i] = ln_mask(ahead.words[i], it.xs);
-        }
-    }
-    if constexpr (ZS == 0) {
-        const LnPick<Q> pick{sm, sc, sp, it.lanes & ~sc.row[1].m[1]};
-        if (ln_any_link(pick)) {
-            T r[4];
-            wall_sums<Q>(o, pick, r);
-            pc.s += r[0];
-            pc.x += r[1];
-            pc.y += r[2];
-            pc.t += r[3];
-        }
-    }
-    // plane zs - 1 is complete: finalise and store the window, solid nodes as zeros
-    if (ZS < 0 || (ZS == 0 && zs > it.z0)) {
-        T d, vx, vy, vz;
-        finish_node<Q>(pm.t, pm.s, m, pm.x, pm.y, it.gx, it.gy, it.gz, d, vx, vy, vz);
-        const bool f = !__builtin_amdgcn_inverse_ballot_w64(sm.row[1].m[1]);
-        if (__builtin_amdgcn_inverse_ballot_w64(it.lanes)) {
-            uint32_t x = it.xb;
-            asm volatile("" : "+v"(x));
-            St::store(reinterpret_cast<S*>(out + x), 0, f ? d : (T)0, it.sr);
-            St::store(reinterpret_cast<S*>(out + it.stride + x), 0, f ? vx : (T)0, it.su);
-            St::store(reinterpret_cast<S*>(out + 2 * it.stride + x), 0, f ? vy : (T)0, it.su);
-            St::store(reinterpret_cast<S*>(out + 3 * it.stride + x), 0, f ? vz : (T)0, it.su);
-        }
-        out += it.plane;
+        for (int k = 0; k < 3; ++k) asm volatile("" : "+s"(r.words[i].w[k]));
+        s.row[i] = ln_mask(r.words[i], it.xs);
     }
 }
 
+// One plane z, with the planes z - 1 and z at hand and the rows of z + 1 in
+// `ahead`; requests plane z + 2's unless z is the segment's last.
+template <int Q, int P>
+__device__ __forceinline__ void ln_step(const LnItem<P>& it, int z,
+                                        const LnPlane<typename Storage<P>::T>& pm,
+                                        const LnPlane<typename Storage<P>::T>& pc,
+                                        LnPlane<typename Storage<P>::T>& pp, const LnSolid& sm,
+                                        const LnSolid& sc, LnSolid& sp, LnRows<P>& ahead, LnAt& at,
+                                        char*& out) {
+#pragma clang fp contract(off)
+    using St = Storage<P>;
+    using T = typename St::T;
+    using S = typename St::S;
+    ln_take(it, ahead, pp, sp);
+    if (z + 1 < it.z1) {
+        ln_next_plane(it, at);
+        ln_request(it, at, ahead);
+    }
+    LnNode<T> n{0, 0, 0, 0};
+    {
+        const LnSrc<T>& o = pc.row[1];
+        n.d += (T)weight<Q>(0) * (o.d + ((T)1 + o.d) * ((T)0 - o.h));
+    }
+    const uint64_t solid = sc.row[1];
+    ln_gather<Q>(pm, pc, pp, sm, sc, sp, it.lanes & ~solid, n);
+    const T r = (T)1 / ((T)1 + n.d);
+    const T ux = n.vx * r + it.gx, uy = n.vy * r + it.gy, uz = n.vz * r + it.gz;
+    // solid nodes are kept as zeros
+    const bool f = !__builtin_amdgcn_inverse_ballot_w64(solid);
+    if (__builtin_amdgcn_inverse_ballot_w64(it.lanes)) {
+        uint32_t x = it.xb;
+        asm volatile("" : "+v"(x));
+        St::store(reinterpret_cast<S*>(out + x), 0, f ? n.d : (T)0, it.sr);
+        St::store(reinterpret_cast<S*>(out + it.stride + x), 0, f ? ux + it.gx : (T)0, it.su);
+        St::store(reinterpret_cast<S*>(out + 2 * it.stride + x), 0, f ? uy + it.gy : (T)0, it.su);
+        St::store(reinterpret_cast<S*>(out + 3 * it.stride + x), 0, f ? uz + it.gz : (T)0, it.su);
+    }
+    out += it.plane;
+}
+
+// Waves per SIMD: as many as the sources of nine rows leave without spilling in
+// the loop (one more: D3Q19 FP64 128^3 52 -> 144 us, FP32 150 x 110 x 90 22.8 ->
+// 23.9; D3Q27 FP32 31.4 -> 37.5).
+constexpr int ln_waves(int q, int p) { return p == kF64 ? (q == 27 ? 2 : 3) : q == 27 ? 4 : 5; }
+
 template <int Q, int P>
 __global__ __launch_bounds__(kLnThreads)
-__attribute__((amdgpu_waves_per_eu(P == kF64 ? 3 : 6))) void k_lines(StepArgs a) {
+__attribute__((amdgpu_waves_per_eu(ln_waves(Q, P)))) void k_lines(StepArgs a) {
     using St = Storage<P>;
     using T = typename St::T;
     using S = typename St::S;
@@ -334,15 +381,14 @@ __attribute__((amdgpu_waves_per_eu(P == kF64 ? 3 : 6))) void k_lines(StepArgs a)
     it.isu = inv_scale_u<P>(a);
     it.sr = scale_rho<P>(a);
     it.su = scale_u<P>(a);
-    it.gx = (T)2 * gh_of<T>(a, 0);
-    it.gy = (T)2 * gh_of<T>(a, 1);
-    it.gz = (T)2 * gh_of<T>(a, 2);
+    it.gx = gh_of<T>(a, 0);
+    it.gy = gh_of<T>(a, 1);
+    it.gz = gh_of<T>(a, 2);
 
-    // bit e of an extended mask row is node e - 1, and lane l's left neighbour
-    // is node x0 - halo + l - 1: bit 0 of the window is bit x0 - halo of the row
-    // (the word before the first row of the mask, for x0 = 0, lies inside the
-    // workspace, and its bit reaches only lane 0's unused left neighbour)
-    const int bit0 = x0 - halo;
+    // bit e of an extended mask row is node e - 1, and lane 0 holds node x0 - halo
+    // (the words past a row's end reach lanes that hold no node; past the last
+    // row lie two words more)
+    const int bit0 = x0 - halo + 1;
     it.xs = bit0 & 31;
     LnAt at;
     at.z = (it.z0 == 0 ? it.nz : it.z0) - 1;
@@ -350,34 +396,26 @@ __attribute__((amdgpu_waves_per_eu(P == kF64 ? 3 : 6))) void k_lines(StepArgs a)
     at.mask = reinterpret_cast<const char*>(a.base + sd->xmask) + (bit0 >> 5) * 4 + at.z * it.mplane;
     char* out = reinterpret_cast<char*>(a.base + sd->state[a.parity ^ 1]) + it.z0 * it.plane + it.row[1];
 
-    LnRows<P> ahead;
+    // planes z0 - 1, z0 and z0 + 1 are requested together
+    LnRows<P> first, second, ahead;
+    ln_request(it, at, first);
+    ln_next_plane(it, at);
+    ln_request(it, at, second);
+    ln_next_plane(it, at);
     ln_request(it, at, ahead);
+    LnPlane<T> A, B, C;
     LnSolid sa, sb, sc;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) sa.row[i] = ln_mask(ahead.words[i], it.xs);
-    LnSum<T> A, B, C;
+    ln_take(it, first, A, sa);
+    ln_take(it, second, B, sb);
     // the three planes' roles rotate statically (unrolled by three)
-    ln_step<Q, P, 1>(it, it.z0 - 1, B, C, A, sc, sa, sb, ahead, at, out);
-    int zs = it.z0;
-    while (true) {
-        ln_step<Q, P, 0>(it, zs, C, A, B, sa, sb, sc, ahead, at, out);
-        if (++zs >= it.z1) {
-            sa = sb;
-            break;
-        }
-        ln_step<Q, P, 0>(it, zs, A, B, C, sb, sc, sa, ahead, at, out);
-        if (++zs >= it.z1) {
-            A = B;
-            sa = sc;
-            break;
-        }
-        ln_step<Q, P, 0>(it, zs, B, C, A, sc, sa, sb, ahead, at, out);
-        if (++zs >= it.z1) {
-            A = C;
-            break;
-        }
+    for (int z = it.z0;;) {
+        ln_step<Q, P>(it, z, A, B, C, sa, sb, sc, ahead, at, out);
+        if (++z >= it.z1) break;
+        ln_step<Q, P>(it, z, B, C, A, sb, sc, sa, ahead, at, out);
+        if (++z >= it.z1) break;
+        ln_step<Q, P>(it, z, C, A, B, sc, sa, sb, ahead, at, out);
+        if (++z >= it.z1) break;
     }
-    ln_step<Q, P, -1>(it, it.z1, A, B, C, sa, sb, sc, ahead, at, out);
 }
 
 #define TAU1_LN_TABLE_DECL(PP) void* ln_kernel_##PP(int q);
@@ -405,9 +443,8 @@ inline void lines_windows(SampleDev& sd) {
 // waves come to about kLnTarget, and each sample's first workgroup (block0).
 // Returns the number of workgroups.  Long segments repeat less work (a segment
 // of n planes reads n + 2), short ones fill the card: measured per step on
-// 128^3 FP64, 2048 waves 47 us, 3072 36 us, 4600 40 us, 6144 36 us; on 150 x
-// 110 x 90 FP32, 2048 22 us, 3072 20 us, 4950 17.5 us, 7590 18.4 us.  FP64 runs
-// at four waves per SIMD, the others at seven.
+// 128^3 FP64, 2048 waves 67 us, 3072 52 us, 4096 59 us, 6144 53 us; on 150 x
+// 110 x 90 FP32, 3072 26 us, 5940 23 us, 9900 23 us.
 constexpr int64_t kLnTarget = 5000, kLnTarget64 = 3072;
 constexpr int kLnMaxLz = 64;
 template <typename SH>
