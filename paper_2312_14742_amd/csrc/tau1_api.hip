@@ -224,7 +224,7 @@ Plan make_plan(const tau1_desc* d, bool tables) {
         p.d2_span = d2q9_steps(p.s.data(), d->n_samples);
         blocks = d2q9_blocks(p.s.data(), d->n_samples, p.d2_span);
     } else {
-        blocks = lines_tiling(p.s.data(), d->n_samples, d->precision);
+        blocks = lines_tiling(p.s.data(), d->n_samples, d->lattice, d->precision);
     }
     // packed layout: by default for the z-march precisions (FP32 and the
     // 16-bit storage modes) unless a dense-layout tile is asked for;

@@ -439,29 +439,50 @@ inline void lines_windows(SampleDev& sd) {
     sd.ln_nodes = (sd.nx + sd.ln_windows - 1) / sd.ln_windows;
 }
 
-// Work of a context's samples for the row kernel: z-segments cut so that the
-// waves come to about kLnTarget, and each sample's first workgroup (block0).
-// Returns the number of workgroups.  Long segments repeat less work (a segment
-// of n planes reads n + 2), short ones fill the card: measured per step on
-// 128^3 FP64, 2048 waves 67 us, 3072 52 us, 4096 59 us, 6144 53 us; on 150 x
-// 110 x 90 FP32, 3072 26 us, 5940 23 us, 9900 23 us.
-constexpr int64_t kLnTarget = 5000, kLnTarget64 = 3072;
+// Modelled time of a step at segments of lz planes, `waves` of them resident per
+// SIMD at a time: a segment marches through lz planes after a start of about one
+// plane's time, each plane takes a SIMD a time that grows with its waves w like
+// 0.5 + w, and a launch runs in rounds of the resident waves.  Over ten lattices
+// (FP64 32^3 to 256 x 256 x 128, FP32 and half storage 50^3 to 300 x 200 x 150)
+// timed at three to ten lengths each, the length chosen is the fastest or within
+// 3 % of it; a count of waves alone is not enough (128^3 FP64, 3 resident: 3072
+// waves 52 us, 4224 59 us, 6144 53 us, 8448 56 us).
+template <typename SH>
+inline double lines_cost(const SH* s, int n, int resident, int lz) {
+    int64_t waves = 0;
+    int longest = 0;
+    for (int i = 0; i < n; ++i) {
+        const SampleDev& sd = s[i].dev;
+        waves += (int64_t)sd.ln_windows * sd.ny * ((sd.nz + lz - 1) / lz);
+        longest = std::max(longest, std::min(lz, sd.nz));
+    }
+    const int64_t per_simd = (waves + 1023) / 1024;
+    const int64_t full = per_simd / resident, rest = per_simd % resident;
+    return (longest + 1) * (full * (1.5 + resident) + (rest ? 1.5 + rest : 0.0));
+}
+
+// Work of a context's samples for the row kernel: the z-segments of the
+// shortest modelled step, and each sample's first workgroup (block0).  Returns
+// the number of workgroups.
 constexpr int kLnMaxLz = 64;
 template <typename SH>
-inline int64_t lines_tiling(SH* s, int n, int precision) {
-    int64_t planes = 0;
-    for (int i = 0; i < n; ++i) {
-        SampleDev& sd = s[i].dev;
-        lines_windows(sd);
-        planes += (int64_t)sd.ln_windows * sd.ny * sd.nz;
+inline int64_t lines_tiling(SH* s, int n, int lattice, int precision) {
+    for (int i = 0; i < n; ++i) lines_windows(s[i].dev);
+    const int resident = ln_waves(lattice, precision);
+    int lz = 1;
+    double best = lines_cost(s, n, resident, 1);
+    for (int c = 2; c <= kLnMaxLz; ++c) {
+        const double t = lines_cost(s, n, resident, c);
+        if (t < best) {
+            best = t;
+            lz = c;
+        }
     }
-    const int64_t target = precision == kF64 ? kLnTarget64 : kLnTarget;
-    const int64_t lz = std::clamp<int64_t>(planes / target, 1, kLnMaxLz);
     int64_t blocks = 0;
     for (int i = 0; i < n; ++i) {
         SampleDev& sd = s[i].dev;
-        const int64_t segs = (sd.nz + lz - 1) / lz;
-        sd.ln_lz = (int32_t)((sd.nz + segs - 1) / segs);
+        const int segs = (sd.nz + lz - 1) / lz;
+        sd.ln_lz = (sd.nz + segs - 1) / segs;
         sd.block0 = blocks;
         const int64_t waves = (int64_t)sd.ln_windows * sd.ny * ((sd.nz + sd.ln_lz - 1) / sd.ln_lz);
         blocks += (waves + kLnWaves - 1) / kLnWaves;
