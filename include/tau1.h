@@ -111,7 +111,9 @@ typedef struct {
     size_t workspace_bytes;
     int32_t kernel;         /* step kernel: -1 = automatic (tuned or default),
                                0 = row kernel (one node per lane, rows of any
-                               length, every precision), 1 = z-march tiles  */
+                               length, every precision; one node per thread
+                               where the rows hold a few nodes only, with the
+                               same bits), 1 = z-march tiles                */
     int32_t tile;           /* z-march tile shape, -1 = automatic (the layout's
                                usual schedule, with z-segments as short as
                                fills the card); 0-15 =

@@ -19,6 +19,7 @@
 #include "tau1_kernels.hpp"
 #include "tau1_zmarch.hpp"
 #include "tau1_lines.hpp"
+#include "tau1_nodes.hpp"
 #include "tau1_readback.hpp"
 #include "tau1_service.hpp"
 
@@ -52,6 +53,7 @@ struct Plan {
     int64_t ntiles = 0;
     int64_t total_blocks = 0;
     int d2_span = 1;           // D2Q9: most steps a launch takes
+    bool nodes = false;        // kernel 0: one node per thread (rows of a few nodes)
     bool packed = false;       // some sample uses the packed layout
     bool pack_refused = false; // packed layout requested but no sample qualifies
     std::vector<SampleHost> s;
@@ -225,6 +227,8 @@ Plan make_plan(const tau1_desc* d, bool tables) {
         blocks = d2q9_blocks(p.s.data(), d->n_samples, p.d2_span);
     } else {
         blocks = lines_tiling(p.s.data(), d->n_samples, d->lattice, d->precision);
+        p.nodes = nodes_faster(p.s.data(), d->n_samples, d->lattice, d->precision);
+        if (p.nodes) blocks = nodes_tiling(p.s.data(), d->n_samples);
     }
     // packed layout: by default for the z-march precisions (FP32 and the
     // 16-bit storage modes) unless a dense-layout tile is asked for;
@@ -501,6 +505,11 @@ Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
     } else if (kernel == 2) {
         l.fn = pick_d2q9(ctx->precision);
         l.block = dim3(kD2Threads);
+        l.grid = dim3((unsigned)ctx->plan.total_blocks);
+        l.shmem = 0;
+    } else if (ctx->plan.nodes) {
+        l.fn = pick_nodes(ctx->lattice, ctx->precision);
+        l.block = dim3(kNodeThreads);
         l.grid = dim3((unsigned)ctx->plan.total_blocks);
         l.shmem = 0;
     } else {

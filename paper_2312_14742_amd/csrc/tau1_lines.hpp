@@ -1,5 +1,5 @@
 // tau1_lines.hpp -- step kernel for rows of any length, in every precision: one
-// node per lane.
+// node per lane (rows of a few nodes: tau1_nodes.hpp).
 //
 // A wave owns a window of at most 62 consecutive x-nodes of one row (plus the
 // node on either side in the first and last lane, periodic in x; rows of 64

@@ -10,6 +10,7 @@
 enum { OK = 0, OUT_OF_MEMORY = 2, CAPTURING = 900 };
 
 unsigned fake_pinned_flags, fake_event_flags;
+int fake_grid;                     /* workgroups of the last launch */
 int fake_launches, fake_graph_builds, fake_graph_nodes, fake_events, fake_pinned, fake_copies;
 int fake_freed_here, fake_freed;   /* hipHostFree: on the main thread, on any */
 int fake_refuse_pinned, fake_capturing;
@@ -71,7 +72,8 @@ int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *l, void **s) {
     return OK;
 }
 int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **a, size_t l, void *s) {
-    (void)f; (void)g; (void)b; (void)a; (void)l; (void)s;
+    (void)f; (void)b; (void)a; (void)l; (void)s;
+    fake_grid = (int)g.x;
     ++fake_launches;
     return OK;
 }
