@@ -173,9 +173,10 @@ typedef struct {
     int32_t tile;            /* tile in use (z-march tiles and the chunk
                                 tile; after an automatic choice, whose
                                 z-segments may be shorter than the tile's,
-                                the nearest one); in a batch, that of the lane layout
-                                with the most fluid nodes (tau1_autotune
-                                gives each layout its own)                 */
+                                the nearest one: asked for by its number it
+                                has its own segments); in a batch, that of
+                                the lane layout with the most fluid nodes
+                                (tau1_autotune gives each layout its own)   */
     int32_t graph_chunk;
     int32_t layout;          /* 1 if any sample is stored packed, else 0    */
     int64_t n_nodes;         /* all samples                                 */

@@ -1296,8 +1296,7 @@ tau1_status tau1_create(const tau1_desc* desc, tau1_ctx** out) {
         if (st == TAU1_OK && ctx->kernel == 1 && desc->tile < 0 && !ctx->cache.empty()) {
             const int t = zmarch_cache_lookup(ctx->cache.c_str(), ctx->lattice, ctx->precision,
                                               ctx->n_nodes, packed);
-            // a cached tile that the automatic choice already goes by stays with it
-            if (t >= 0 && t != ctx->tile) st = set_tile(ctx, t, nullptr, ctx->merge_rows);
+            if (t >= 0) st = set_tile(ctx, t, nullptr, ctx->merge_rows);
         }
         if (st != TAU1_OK) {
             delete ctx;
@@ -1514,11 +1513,10 @@ tau1_status tau1_autotune(tau1_ctx* ctx, int32_t trial_steps) {
     st = merged_tile >= 0 ? set_tile(ctx, merged_tile, nullptr, true)
                           : set_tile(ctx, best_tile, tile_v.data(), ctx->merge_rows);
     if (st != TAU1_OK) return st;
-    // the cache keeps one tile per size bucket: the best single tile (of an
-    // automatic choice, the one the context now goes by)
+    // the cache keeps one tile per size bucket: the best single one
     if (!ctx->cache.empty())
         zmarch_cache_store(ctx->cache.c_str(), ctx->lattice, ctx->precision, ctx->n_nodes,
-                           best_tile == kAutoTile ? ctx->tile : best_tile, best / trial_steps);
+                           best_tile, best / trial_steps);
     return TAU1_OK;
 }
 

@@ -1511,7 +1511,9 @@ inline int zmarch_segment(const SH* s, int n, int variant, bool blocks, int resi
     return best_lz;
 }
 
-// Autotune cache: one line per entry "tau1 <arch> q<Q> p<P> n<bucket> tile <t> ms <x>".
+// Autotune cache: one line per entry "tau1 <arch> q<Q> p<P> n<bucket> tile <t> ms
+// <x>", t a tile's number or "auto" for the automatic choice, whose segments
+// depend on the lattice.
 inline int64_t size_bucket(int64_t n) {
     int64_t b = 1;
     while (b < n) b <<= 1;
@@ -1525,15 +1527,20 @@ inline int zmarch_cache_lookup(const char* path, int q, int p, int64_t nodes, bo
     int found = -1;
     const int64_t bucket = size_bucket(nodes);
     while (std::fgets(line, sizeof line, f)) {
-        int qq, pp, tile;
+        int qq, pp;
+        char name[16];
         long long nb;
         float ms;
         char arch[64];
-        if (std::sscanf(line, "tau1 %63s q%d p%d n%lld tile %d ms %f", arch, &qq, &pp, &nb, &tile,
-                        &ms) == 6 &&
-            std::strcmp(arch, "gfx950") == 0 && qq == q && pp == p && nb == bucket &&
-            zmarch_tile_ok(p, packed, tile))
-            found = tile;
+        if (std::sscanf(line, "tau1 %63s q%d p%d n%lld tile %15s ms %f", arch, &qq, &pp, &nb, name,
+                        &ms) != 6 ||
+            std::strcmp(arch, "gfx950") != 0 || qq != q || pp != p || nb != bucket)
+            continue;
+        char* end;
+        const long t = std::strtol(name, &end, 10);
+        if (std::strcmp(name, "auto") == 0) found = kAutoTile;
+        else if (end != name && *end == 0 && t >= 0 && t < kNumTiles && zmarch_tile_ok(p, packed, (int)t))
+            found = (int)t;
     }
     std::fclose(f);
     return found;
@@ -1542,8 +1549,9 @@ inline int zmarch_cache_lookup(const char* path, int q, int p, int64_t nodes, bo
 inline void zmarch_cache_store(const char* path, int q, int p, int64_t nodes, int tile, float ms) {
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "tau1 gfx950 q%d p%d n%lld tile %d ms %.6f\n", q, p,
-                 (long long)size_bucket(nodes), tile, ms);
+    const std::string name = tile == kAutoTile ? "auto" : std::to_string(tile);
+    std::fprintf(f, "tau1 gfx950 q%d p%d n%lld tile %s ms %.6f\n", q, p,
+                 (long long)size_bucket(nodes), name.c_str(), ms);
     std::fclose(f);
 }
 
