@@ -1218,22 +1218,16 @@ void k_zmarch(StepArgs a) {
     const int per = (nwg + 7) / 8;
     const int xcd = b % 8, k = b / 8;
     const int lb = xcd * per + k;
-    const int nwaves = ((nwg + 7) / 8) * 8 * kZrWaves;
     // the item index is uniform across the wave; say so, so that every
     // per-item quantity (sample descriptor, buffer resources) stays scalar
-    const int first = __builtin_amdgcn_readfirstlane(lb * kZrWaves + wave);
-    for (int item = first; item < a.ntiles; item += nwaves) {
-        // the work list is constant while a step runs: a scalar load
-        typedef int wi4 __attribute__((ext_vector_type(4)));
-        typedef const __attribute__((address_space(4))) wi4 item_t;
-        const wi4 t = ((item_t*)a.tiles)[item];
-        // the row slots are written before a plane's one barrier: the item
-        // before is read to its end by all four waves first (its last plane's
-        // slot may be the first one written)
-        if (kShare && item != first) __syncthreads();
-        zr_item<Q, P, G, C, K, NL, MODE, zr_early(Q, P, V, MODE)>(a, a.samples + t.x, t.y, t.z,
-                                                                 t.w, lds_wave, wave, lds_all);
-    }
+    const int item = __builtin_amdgcn_readfirstlane(lb * kZrWaves + wave);
+    if (item >= a.ntiles) return;  // shared rows: all four waves or none
+    // the work list is constant while a step runs: a scalar load
+    typedef int wi4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(4))) wi4 item_t;
+    const wi4 t = ((item_t*)a.tiles)[item];
+    zr_item<Q, P, G, C, K, NL, MODE, zr_early(Q, P, V, MODE)>(a, a.samples + t.x, t.y, t.z, t.w,
+                                                             lds_wave, wave, lds_all);
 }
 
 // Lane layouts of the one-launch kernel: one row per wave in one chunk (rows
@@ -1290,17 +1284,13 @@ void k_zmarch_rows(StepArgs a) {
     const int per = (nwg + 7) / 8;
     const int xcd = b % 8, k = b / 8;
     const int lb = xcd * per + k;
-    const int nwaves = ((nwg + 7) / 8) * 8 * kZrWaves;
-    const int first = __builtin_amdgcn_readfirstlane(lb * kZrWaves + wave);
-    for (int item = first; item < a.ntiles; item += nwaves) {
-        typedef int wi4 __attribute__((ext_vector_type(4)));
-        typedef const __attribute__((address_space(4))) wi4 item_t;
-        const wi4 t = ((item_t*)a.tiles)[item];
-        const int v = __builtin_amdgcn_readfirstlane(a.samples[t.x].variant);
-        // as in k_zmarch; here the slots also move with the layout's row length
-        if (item != first) __syncthreads();
-        zr_rows_item<Q, P, MODE>(a, v, t.x, t.y, t.z, t.w, lds_all, wave);
-    }
+    const int item = __builtin_amdgcn_readfirstlane(lb * kZrWaves + wave);
+    if (item >= a.ntiles) return;
+    typedef int wi4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(4))) wi4 item_t;
+    const wi4 t = ((item_t*)a.tiles)[item];
+    const int v = __builtin_amdgcn_readfirstlane(a.samples[t.x].variant);
+    zr_rows_item<Q, P, MODE>(a, v, t.x, t.y, t.z, t.w, lds_all, wave);
 }
 
 // Kernel table of one (lattice, precision) pair; defined in the per-pair
@@ -1373,13 +1363,14 @@ inline void* pick_zmarch_rows(int q, int p, int mode) {
     return nullptr;
 }
 
-// Resident-sized grid: at most enough workgroups for every item, rounded to
-// whole XCD rounds.
+// One workgroup per four items, rounded to whole XCD rounds.  (With at most 2048
+// workgroups the rest of a longer list was a second item for the first of them,
+// which the XCD-aware order puts on the same XCDs: 512 x 300 x 511 at segments of
+// 16 planes, 2400 workgroups' worth, 730 us a step with the limit, 528 without.
+// It also took a barrier between the two items.)
 inline int64_t zmarch_grid(int64_t nitems) {
     const int64_t wgs = (nitems + kZrWaves - 1) / kZrWaves;
-    const int64_t cap = 256 * 8;  // 256 CUs x up to 8 workgroups resident
-    int64_t g = wgs < cap ? wgs : cap;
-    return (g + 7) / 8 * 8;
+    return (wgs + 7) / 8 * 8;
 }
 
 // Supported when every sample has a lane layout and each state array and

@@ -1,8 +1,8 @@
-"""Shared-row z-march launches whose workgroups take several work items (more
-than 2048 blocks of four rows): the next item's first rows go to the LDS slots
-that the waves read at the end of the item before.  An item that ends at an
-odd plane and one that starts at an even plane use the same slot.  The bits
-have to be those of segments long enough for one item per workgroup."""
+"""Shared-row z-march launches of more than 2048 blocks of four rows, far more than
+are resident at a time.  (Where a workgroup takes two blocks, the second one's
+first rows go to the LDS slots that the waves still read at the end of the
+first: an item that ends at an odd plane and one that starts at an even plane
+use the same slot.)  The bits have to be those of a few long segments."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,7 @@ from paper_2312_14742_amd import inputs, tau1
 pytestmark = pytest.mark.gpu
 
 G = (1e-5, -2e-5, 3e-6)
-GRID = 2048     # workgroups a launch has at most
+GRID = 2048
 
 
 def blocks(sim):
