@@ -68,7 +68,7 @@ G_MAIN = (1e-6, 0.0, 0.0)
 POROSITIES = (0.05, 0.1, 0.2, 0.3, 0.5, 0.6, 0.7, 0.8, 0.9)
 COUNTERS = os.path.join(ROOT, "profiles", "zmarch_d3q19_f32_512cube_phi07.counters.txt")
 CHUNK_TILE = 16                # the step over stored chunks (packed layout)
-KERNEL_SOURCES = ("tau1_device.hpp", "tau1_args.hpp", "tau1_zmarch.hpp",
+KERNEL_SOURCES = ("tau1_device.hpp", "tau1_args.hpp", "tau1_sums.hpp", "tau1_zmarch.hpp",
                   "tau1_zmarch_inst.hip")
 
 

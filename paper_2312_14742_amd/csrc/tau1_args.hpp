@@ -1,5 +1,5 @@
 // tau1_args.hpp -- launch arguments shared by every step kernel (the z-march
-// tiles, the per-node gather, the D2Q9 kernel) and the service kernels, with
+// tiles, the row and node kernels, the D2Q9 kernel) and the service kernels, with
 // the storage-scale accessors the kernels read them through.
 #pragma once
 
@@ -16,7 +16,7 @@ struct StepArgs {
     int32_t nsamples;
     int32_t parity;             // buffer read this step; the other is written
     int32_t ntiles;             // z-march work items
-    int32_t lblocks;            // row kernel: workgroups holding work
+    int32_t lblocks;            // row and node kernels: workgroups holding work
     double gh[3];               // g / 2 (FP64)
     float ghf[3];               // g / 2 (FP32)
     float scale_rho, inv_scale_rho, scale_u, inv_scale_u;  // F16 storage

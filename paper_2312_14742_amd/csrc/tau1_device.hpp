@@ -27,6 +27,7 @@ template <int Q> struct Lattice;
 
 template <> struct Lattice<19> {
     static constexpr int q = 19;
+    static constexpr int units = 36;  // the weights are whole multiples of 1 / units
     static constexpr Dir c[19] = {
         {0, 0, 0},
         {1, 0, 0}, {-1, 0, 0}, {0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1},
@@ -39,6 +40,7 @@ template <> struct Lattice<19> {
 
 template <> struct Lattice<15> {
     static constexpr int q = 15;
+    static constexpr int units = 72;  // the weights are whole multiples of 1 / units
     static constexpr Dir c[15] = {
         {0, 0, 0},
         {1, 0, 0}, {-1, 0, 0}, {0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1},
@@ -50,6 +52,7 @@ template <> struct Lattice<15> {
 
 template <> struct Lattice<27> {
     static constexpr int q = 27;
+    static constexpr int units = 216;  // the weights are whole multiples of 1 / units
     static constexpr Dir c[27] = {
         {0, 0, 0},
         {1, 0, 0}, {-1, 0, 0}, {0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1},

@@ -3,38 +3,41 @@
 //
 // A wave owns a window of at most 62 consecutive x-nodes of one row (plus the
 // node on either side in the first and last lane, periodic in x; rows of 64
-// nodes need no such lanes) and marches along z over a segment of planes,
-// holding the sources of rows y - 1, y, y + 1 in planes z - 1, z, z + 1.  Per
-// plane it reads the three rows of the plane two ahead with one coalesced load
-// per row and array; what arrives from x +- 1 is formed in the source's lane and
-// moves one lane by DPP.
+// nodes need no such lanes) and marches along z over a segment of planes.  It
+// reads the window of rows y - 1, y, y + 1 with one coalesced load per row and
+// array, requested ahead of its use; what goes to x +- 1 moves one lane by DPP.
 //
-// Arithmetic: each node adds what arrives direction by direction, in the
-// lattice's order, every operation rounded by itself and one division a node.
-// This is the plain evaluation of Eqs. (3) and (9)-(11) that FP64 mode is the
-// reference by: with g = 0 its bits are the oracle's, and FP32 and 16-bit
-// storage are the same operations in FP32.
+// Two forms of the arithmetic:
+//
+// FP64 is the reference of the other modes: each node adds what arrives
+// direction by direction, in the lattice's order, every operation rounded by
+// itself and one division a node.  This is the plain evaluation of Eqs. (3) and
+// (9)-(11); with g = 0 its bits are the oracle's.  The wave holds the sources of
+// nine rows (planes z - 1, z, z + 1) and finishes one plane at a time, each
+// direction formed in the source's lane.
+//
+// FP32, and 16-bit storage, sum by groups of directions (tau1_sums.hpp): a third
+// of the instructions, and the smaller error.  The wave holds the three rows of
+// one source plane at a time and sends each group to the planes z - 1, z, z + 1.
 //
 // Solid links need no vector work to be found: with one node per lane, the
 // solid bits of a row window are a lane mask.  They are read with scalar loads
 // from the extended mask, rotated on the scalar unit, and select each
-// bounced-back value with one v_cndmask; a pair of opposite directions without
-// a link in the window skips its own values.
+// bounced-back value with one v_cndmask; a window (FP64: a pair of opposite
+// directions) without a link skips its own values.
 //
-// What bounds it: vector issue (about 500 instructions a node and plane on
-// D3Q19, wall returns included) at the share of lanes that a row fills, and on
-// small lattices the three planes in a row that a segment's first result needs,
-// so segments are cut until the waves fill the card (lines_tiling).  Measured
-// per step against a pull kernel with one thread per node, which read 76 values
-// and formed 64-bit addresses and zero-component products for each: 32^3 FP64
-// 8.4 -> 4.6 us, porous 128^3 FP64 135 -> 53 us, porous 150 x 110 x 90 FP32 56
-// -> 23 us.  (Sums by groups of directions with fused multiply-adds took 3.9,
-// 36 and 17.5 us, at about twice the FP64 error.)
+// What bounds it: vector issue (D3Q19, a node and plane, wall returns included:
+// about 500 instructions in FP64, 220 in FP32) at the share of lanes that a row
+// fills, and on small lattices the planes in a row that a segment takes, so
+// segments are cut until the waves fill the card (lines_tiling).  Measured per
+// step against one thread per node, which read 76 values and formed 64-bit
+// addresses and zero-component products for each: 32^3 FP64 8.4 -> 4.5 us, porous
+// 128^3 FP64 135 -> 53 us, porous 150 x 110 x 90 FP32 56 -> 18 us.
 #pragma once
 
 #include <algorithm>
 
-#include "tau1_args.hpp"
+#include "tau1_sums.hpp"
 
 namespace tau1 {
 
@@ -90,7 +93,7 @@ struct LnItem {
     uint32_t xb;                // byte offset of the lane's node in its row
     uint64_t lanes;             // lanes whose node belongs to the window
     T isr, isu, sr, su;
-    T gx, gy, gz;               // g / 2
+    T gx, gy, gz;               // g / 2 (FP64), g (FP32)
 };
 
 // The march's position: plane to be requested next.
@@ -268,20 +271,45 @@ __device__ __forceinline__ void ln_request(const LnItem<P>& it, const LnAt& at, 
     }
 }
 
-// The rows of a requested plane, landed: sources and solid bits.
+// Solid bits of a requested plane's rows, landed.
 template <int P>
-__device__ __forceinline__ void ln_take(const LnItem<P>& it, LnRows<P>& r,
-                                        LnPlane<typename Storage<P>::T>& p, LnSolid& s) {
+__device__ __forceinline__ void ln_solid(const LnItem<P>& it, LnRows<P>& r, LnSolid& s) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        p.row[i] = ln_src(it, r.row[i]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) asm volatile("" : "+s"(r.words[i].w[k]));
         s.row[i] = ln_mask(r.words[i], it.xs);
     }
 }
 
-// One plane z, with the planes z - 1 and z at hand and the rows of z + 1 in
+// FP64: the rows of a requested plane, landed: sources and solid bits.
+template <int P>
+__device__ __forceinline__ void ln_take(const LnItem<P>& it, LnRows<P>& r,
+                                        LnPlane<typename Storage<P>::T>& p, LnSolid& s) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p.row[i] = ln_src(it, r.row[i]);
+    ln_solid(it, r, s);
+}
+
+// Stores a window of finished nodes, solid ones as zeros.
+template <int P>
+__device__ __forceinline__ void ln_store(const LnItem<P>& it, char* out,
+                                         const LnNode<typename Storage<P>::T>& n, uint64_t solid) {
+    using St = Storage<P>;
+    using T = typename St::T;
+    using S = typename St::S;
+    const bool f = !__builtin_amdgcn_inverse_ballot_w64(solid);
+    if (__builtin_amdgcn_inverse_ballot_w64(it.lanes)) {
+        uint32_t x = it.xb;
+        asm volatile("" : "+v"(x));
+        St::store(reinterpret_cast<S*>(out + x), 0, f ? n.d : (T)0, it.sr);
+        St::store(reinterpret_cast<S*>(out + it.stride + x), 0, f ? n.vx : (T)0, it.su);
+        St::store(reinterpret_cast<S*>(out + 2 * it.stride + x), 0, f ? n.vy : (T)0, it.su);
+        St::store(reinterpret_cast<S*>(out + 3 * it.stride + x), 0, f ? n.vz : (T)0, it.su);
+    }
+}
+
+// FP64: one plane z, with the planes z - 1 and z at hand and the rows of z + 1 in
 // `ahead`; requests plane z + 2's unless z is the segment's last.
 template <int Q, int P>
 __device__ __forceinline__ void ln_step(const LnItem<P>& it, int z,
@@ -291,9 +319,7 @@ __device__ __forceinline__ void ln_step(const LnItem<P>& it, int z,
                                         const LnSolid& sc, LnSolid& sp, LnRows<P>& ahead, LnAt& at,
                                         char*& out) {
 #pragma clang fp contract(off)
-    using St = Storage<P>;
-    using T = typename St::T;
-    using S = typename St::S;
+    using T = typename Storage<P>::T;
     ln_take(it, ahead, pp, sp);
     if (z + 1 < it.z1) {
         ln_next_plane(it, at);
@@ -307,24 +333,119 @@ __device__ __forceinline__ void ln_step(const LnItem<P>& it, int z,
     const uint64_t solid = sc.row[1];
     ln_gather<Q>(pm, pc, pp, sm, sc, sp, it.lanes & ~solid, n);
     const T r = (T)1 / ((T)1 + n.d);
-    const T ux = n.vx * r + it.gx, uy = n.vy * r + it.gy, uz = n.vz * r + it.gz;
-    // solid nodes are kept as zeros
-    const bool f = !__builtin_amdgcn_inverse_ballot_w64(solid);
-    if (__builtin_amdgcn_inverse_ballot_w64(it.lanes)) {
-        uint32_t x = it.xb;
-        asm volatile("" : "+v"(x));
-        St::store(reinterpret_cast<S*>(out + x), 0, f ? n.d : (T)0, it.sr);
-        St::store(reinterpret_cast<S*>(out + it.stride + x), 0, f ? ux + it.gx : (T)0, it.su);
-        St::store(reinterpret_cast<S*>(out + 2 * it.stride + x), 0, f ? uy + it.gy : (T)0, it.su);
-        St::store(reinterpret_cast<S*>(out + 3 * it.stride + x), 0, f ? uz + it.gz : (T)0, it.su);
-    }
+    n.vx = (n.vx * r + it.gx) + it.gx;
+    n.vy = (n.vy * r + it.gy) + it.gy;
+    n.vz = (n.vz * r + it.gz) + it.gz;
+    ln_store(it, out, n, solid);
     out += it.plane;
 }
 
-// Waves per SIMD: as many as the sources of nine rows leave without spilling in
-// the loop (one more: D3Q19 FP64 128^3 52 -> 144 us, FP32 150 x 110 x 90 22.8 ->
-// 23.9; D3Q27 FP32 31.4 -> 37.5).
-constexpr int ln_waves(int q, int p) { return p == kF64 ? (q == 27 ? 2 : 3) : q == 27 ? 4 : 5; }
+// FP32: the sums of one node in one destination plane.
+struct LnSum {
+    float t, s, x, y;
+};
+
+template <int Q, int CY, int CZ>
+__device__ __forceinline__ void ln_group(const Src& s, float f, float g, LnSum& q, float& m) {
+    using G = Group<Q, CY, CZ>;
+    if constexpr (G::has0 || G::hasx) {
+        level_z<CZ>(s, f, g);
+        float a = 0.0f, b = 0.0f;
+        if constexpr (G::hasx) {
+            float fp, fm;
+            level_x(s, f, g, fp, fm);
+            a = ln_prev(fp);
+            b = ln_next(fm);
+        }
+        add_group<Q, CY, CZ>(group_sum<Q, CY, CZ>(f, a, b), G::hasx ? a - b : 0.0f, q.t, q.s, q.x,
+                             q.y, m);
+    }
+}
+
+// A source row's directions c_y = CY; ZS as in the z-march's step: 0 = a plane
+// of the segment, +1 / -1 = the plane before / after it (to one plane only).
+template <int Q, int CY, int ZS>
+__device__ __forceinline__ void ln_push(const Src& s, LnSum& pm, LnSum& pc, LnSum& pp, float& m) {
+    float f, g;
+    level_y<CY>(s, f, g);
+    if constexpr (ZS == 0) ln_group<Q, CY, 0>(s, f, g, pc, m);
+    if constexpr (ZS >= 0) ln_group<Q, CY, 1>(s, f, g, pp, m);
+    if constexpr (ZS <= 0) ln_group<Q, CY, -1>(s, f, g, pm, m);
+}
+
+// The selection of wall_sums: direction k's value in the lanes whose neighbour
+// x + c_k is solid (fluid: the window's fluid nodes).
+template <int Q>
+struct LnPick {
+    const LnSolid &sm, &sc, &sp;
+    uint64_t fluid;
+    template <typename K>
+    __device__ __forceinline__ uint64_t links(K) const {
+        return ln_links<Q, K::value>(sm, sc, sp) & fluid;
+    }
+    template <typename K>
+    __device__ __forceinline__ float operator()(K k, float u) const {
+        return __builtin_amdgcn_inverse_ballot_w64(links(k)) ? u : 0.0f;
+    }
+};
+
+template <int Q, int K = 1>
+__device__ __forceinline__ uint64_t ln_any_link(const LnPick<Q>& p) {
+    if constexpr (K >= Q) return 0;
+    else return p.links(std::integral_constant<int, K>{}) | ln_any_link<Q, K + 1>(p);
+}
+
+template <int P>
+__device__ __forceinline__ Src ln_src32(const LnItem<P>& it, const LnNode<typename Storage<P>::S>& r) {
+    using St = Storage<P>;
+    return make_src(St::load(&r.d, 0, it.isr), St::load(&r.vx, 0, it.isu), St::load(&r.vy, 0, it.isu),
+                    St::load(&r.vz, 0, it.isu));
+}
+
+// FP32: one source plane zs, whose rows are in `ahead`; requests plane zs + 1's
+// rows unless it is the last.  sm, sc: solid bits of planes zs - 1 and zs; sp
+// receives those of zs + 1.
+template <int Q, int P, int ZS>
+__device__ __forceinline__ void ln_sstep(const LnItem<P>& it, int zs, LnSum& pm, LnSum& pc, LnSum& pp,
+                                         const LnSolid& sm, const LnSolid& sc, LnSolid& sp,
+                                         LnRows<P>& ahead, LnAt& at, char*& out) {
+    using St = Storage<P>;
+    using S = typename St::S;
+    const Src m1 = ln_src32(it, ahead.row[0]), o = ln_src32(it, ahead.row[1]),
+              p1 = ln_src32(it, ahead.row[2]);
+    if constexpr (ZS >= 0) {
+        ln_next_plane(it, at);
+        ln_request(it, at, ahead);
+    }
+    float m = 0.0f;
+    ln_push<Q, 0, ZS>(o, pm, pc, pp, m);
+    ln_push<Q, 1, ZS>(m1, pm, pc, pp, m);
+    ln_push<Q, -1, ZS>(p1, pm, pc, pp, m);
+    if constexpr (ZS >= 0) ln_solid(it, ahead, sp);  // the mask words have landed meanwhile
+    if constexpr (ZS == 0) {
+        const LnPick<Q> pick{sm, sc, sp, it.lanes & ~sc.row[1]};
+        if (ln_any_link(pick)) {
+            float r[4];
+            wall_sums<Q>(o, pick, r);
+            pc.s += r[0];
+            pc.x += r[1];
+            pc.y += r[2];
+            pc.t += r[3];
+        }
+    }
+    // plane zs - 1 is complete: finalise and store the window
+    if (ZS < 0 || (ZS == 0 && zs > it.z0)) {
+        LnNode<float> n;
+        finish_node<Q>(pm.t, pm.s, m, pm.x, pm.y, it.gx, it.gy, it.gz, n.d, n.vx, n.vy, n.vz);
+        ln_store(it, out, n, sm.row[1]);
+        out += it.plane;
+    }
+}
+
+// Waves per SIMD: in FP64 as many as the sources of nine rows leave without
+// spilling in the loop (one more: D3Q19 128^3 52 -> 144 us); FP32 takes 51-60
+// registers, which is all eight.
+constexpr int ln_waves(int q, int p) { return p == kF64 ? (q == 27 ? 2 : 3) : 8; }
 
 template <int Q, int P>
 __global__ __launch_bounds__(kLnThreads)
@@ -381,9 +502,10 @@ __attribute__((amdgpu_waves_per_eu(ln_waves(Q, P)))) void k_lines(StepArgs a) {
     it.isu = inv_scale_u<P>(a);
     it.sr = scale_rho<P>(a);
     it.su = scale_u<P>(a);
-    it.gx = gh_of<T>(a, 0);
-    it.gy = gh_of<T>(a, 1);
-    it.gz = gh_of<T>(a, 2);
+    constexpr T gs = P == kF64 ? 1 : 2;
+    it.gx = gs * gh_of<T>(a, 0);
+    it.gy = gs * gh_of<T>(a, 1);
+    it.gz = gs * gh_of<T>(a, 2);
 
     // bit e of an extended mask row is node e - 1, and lane 0 holds node x0 - halo
     // (the words past a row's end reach lanes that hold no node; past the last
@@ -396,25 +518,54 @@ __attribute__((amdgpu_waves_per_eu(ln_waves(Q, P)))) void k_lines(StepArgs a) {
     at.mask = reinterpret_cast<const char*>(a.base + sd->xmask) + (bit0 >> 5) * 4 + at.z * it.mplane;
     char* out = reinterpret_cast<char*>(a.base + sd->state[a.parity ^ 1]) + it.z0 * it.plane + it.row[1];
 
-    // planes z0 - 1, z0 and z0 + 1 are requested together
-    LnRows<P> first, second, ahead;
-    ln_request(it, at, first);
-    ln_next_plane(it, at);
-    ln_request(it, at, second);
-    ln_next_plane(it, at);
-    ln_request(it, at, ahead);
-    LnPlane<T> A, B, C;
-    LnSolid sa, sb, sc;
-    ln_take(it, first, A, sa);
-    ln_take(it, second, B, sb);
-    // the three planes' roles rotate statically (unrolled by three)
-    for (int z = it.z0;;) {
-        ln_step<Q, P>(it, z, A, B, C, sa, sb, sc, ahead, at, out);
-        if (++z >= it.z1) break;
-        ln_step<Q, P>(it, z, B, C, A, sb, sc, sa, ahead, at, out);
-        if (++z >= it.z1) break;
-        ln_step<Q, P>(it, z, C, A, B, sc, sa, sb, ahead, at, out);
-        if (++z >= it.z1) break;
+    if constexpr (P == kF64) {
+        // planes z0 - 1, z0 and z0 + 1 are requested together
+        LnRows<P> first, second, ahead;
+        ln_request(it, at, first);
+        ln_next_plane(it, at);
+        ln_request(it, at, second);
+        ln_next_plane(it, at);
+        ln_request(it, at, ahead);
+        LnPlane<T> A, B, C;
+        LnSolid sa, sb, sc;
+        ln_take(it, first, A, sa);
+        ln_take(it, second, B, sb);
+        // the three planes' roles rotate statically (unrolled by three)
+        for (int z = it.z0;;) {
+            ln_step<Q, P>(it, z, A, B, C, sa, sb, sc, ahead, at, out);
+            if (++z >= it.z1) break;
+            ln_step<Q, P>(it, z, B, C, A, sb, sc, sa, ahead, at, out);
+            if (++z >= it.z1) break;
+            ln_step<Q, P>(it, z, C, A, B, sc, sa, sb, ahead, at, out);
+            if (++z >= it.z1) break;
+        }
+    } else {
+        LnRows<P> ahead;
+        ln_request(it, at, ahead);
+        LnSolid sa, sb, sc;
+        ln_solid(it, ahead, sa);
+        LnSum A, B, C;
+        ln_sstep<Q, P, 1>(it, it.z0 - 1, B, C, A, sc, sa, sb, ahead, at, out);
+        int zs = it.z0;
+        while (true) {
+            ln_sstep<Q, P, 0>(it, zs, C, A, B, sa, sb, sc, ahead, at, out);
+            if (++zs >= it.z1) {
+                sa = sb;
+                break;
+            }
+            ln_sstep<Q, P, 0>(it, zs, A, B, C, sb, sc, sa, ahead, at, out);
+            if (++zs >= it.z1) {
+                A = B;
+                sa = sc;
+                break;
+            }
+            ln_sstep<Q, P, 0>(it, zs, B, C, A, sc, sa, sb, ahead, at, out);
+            if (++zs >= it.z1) {
+                A = C;
+                break;
+            }
+        }
+        ln_sstep<Q, P, -1>(it, it.z1, A, B, C, sa, sb, sc, ahead, at, out);
     }
 }
 

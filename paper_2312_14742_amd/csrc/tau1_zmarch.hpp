@@ -42,13 +42,7 @@
 #include <string>
 #include <vector>
 
-#include "tau1_args.hpp"
-
-// Multiply-adds fuse only where one expression writes a * b + c (and at the
-// explicit fmaf calls), never across statements: every tile and load
-// schedule then forms each sum with the same roundings, so results do not
-// depend on the tile the autotuner picks.
-#pragma clang fp contract(on)
+#include "tau1_sums.hpp"
 
 namespace tau1 {
 
@@ -295,28 +289,6 @@ template <int PX>
 struct RawRow {
     float d[PX], vx[PX], vy[PX], vz[PX];
 };
-
-// Per-source quantities: the equilibrium of Eq. (3) minus its weight in a
-// direction with cu = c.v is w * (A + cu * (R3 + R45 * cu)) with
-// A = drho - 1.5 rho v.v, R3 = 3 rho, R45 = 1.5 R3 (= 4.5 rho), rho = 1 + drho.
-// R45 is always formed from R3, so a source shared as (A, R3, v) gives the
-// same bits wherever it is evaluated.
-struct Src {
-    float a, r3, r45, vx, vy, vz;
-};
-
-__device__ __forceinline__ Src make_src(float d, float vx, float vy, float vz) {
-    Src s;
-    const float rho = 1.0f + d;
-    const float vv = vx * vx + vy * vy + vz * vz;
-    s.a = __builtin_fmaf(-1.5f * rho, vv, d);
-    s.r3 = 3.0f * rho;
-    s.r45 = 1.5f * s.r3;
-    s.vx = vx;
-    s.vy = vy;
-    s.vz = vz;
-    return s;
-}
 
 // Components of a source kept in a shared LDS row slot: A, R3, vx, vy, vz.
 constexpr int kSlotComps = 5;

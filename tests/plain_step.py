@@ -1,6 +1,5 @@
-"""One Tau1 step in numpy, direction by direction in the lattice's order with
-every operation rounded by itself, in FP64 or FP32 (storage FP32 or scaled
-half): the arithmetic of the kernels that work node by node."""
+"""One Tau1 step in numpy, FP64: direction by direction in the lattice's order with
+every operation rounded by itself, as kernel 0 does in FP64 mode."""
 import numpy as np
 
 import oracle
@@ -8,34 +7,20 @@ import oracle
 WEIGHTS = {15: (2.0 / 9.0, 1.0 / 9.0, 0.0, 1.0 / 72.0),
            19: (1.0 / 3.0, 1.0 / 18.0, 1.0 / 36.0, 0.0),
            27: (8.0 / 27.0, 2.0 / 27.0, 1.0 / 54.0, 1.0 / 216.0)}
-HALF = 2.0 ** 16       # default scale of the half storage
 
 
-def store(x, prec):
-    """x as the state holds it, back in the compute type."""
-    if prec == "f16":
-        return (x * np.float32(HALF)).astype(np.float16).astype(np.float32) * np.float32(1 / HALF)
-    return x
-
-
-def start(solid, drho, u, g, prec):
+def start(solid, drho, u, g):
     """Initial state (drho, v = u + g/2)."""
-    T = np.float64 if prec == "f64" else np.float32
     fl = solid == 0
-    gh = [T(0.5 * x) for x in g]
-    d = np.where(fl, drho.astype(T), T(0))
-    v = np.stack([np.where(fl, u[a].astype(T) + gh[a], T(0)) for a in range(3)])
-    return store(d, prec), store(v, prec)
+    return drho * fl, np.stack([np.where(fl, u[a] + 0.5 * g[a], 0.0) for a in range(3)])
 
 
-def step(q, solid, d, v, g, prec):
-    T = np.float64 if prec == "f64" else np.float32
-    gh = [T(0.5 * x) for x in g]
-    one, three, c45, c15 = T(1), T(3), T(4.5), T(1.5)
+def step(q, solid, d, v, g):
+    gh = [0.5 * x for x in g]
     n, j = np.zeros_like(d), np.zeros_like(v)
     for c in oracle.lattice(q)[0]:
         cx, cy, cz = (int(x) for x in c)
-        w = T(WEIGHTS[q][abs(cx) + abs(cy) + abs(cz)])
+        w = WEIGHTS[q][abs(cx) + abs(cy) + abs(cz)]
 
         def src(a):
             return np.roll(a, (cz, cy, cx), axis=(0, 1, 2))
@@ -43,22 +28,20 @@ def step(q, solid, d, v, g, prec):
         wall = src(solid) != 0
         ds = np.where(wall, d, src(d))
         vx, vy, vz = (np.where(wall, v[a], src(v[a])) for a in range(3))
-        sign = np.where(wall, T(-1), T(1))
-        rho = one + ds
-        cu = (sign * T(cx) * vx + sign * T(cy) * vy) + sign * T(cz) * vz
+        sign = np.where(wall, -1.0, 1.0)
+        cu = (sign * cx * vx + sign * cy * vy) + sign * cz * vz
         vv = (vx * vx + vy * vy) + vz * vz
-        p = (three * cu + (c45 * cu) * cu) - c15 * vv
-        f = w * (ds + rho * p)
+        p = (3.0 * cu + (4.5 * cu) * cu) - 1.5 * vv
+        f = w * (ds + (1.0 + ds) * p)
         n = n + f
-        j = np.stack([j[0] + T(cx) * f, j[1] + T(cy) * f, j[2] + T(cz) * f])
-    r = one / (one + n)
+        j = np.stack([j[0] + cx * f, j[1] + cy * f, j[2] + cz * f])
+    r = 1.0 / (1.0 + n)
     out = np.stack([(j[a] * r + gh[a]) + gh[a] for a in range(3)])
     fl = solid == 0
-    return store(np.where(fl, n, T(0)), prec), store(np.where(fl, out, T(0)), prec)
+    return np.where(fl, n, 0.0), np.where(fl, out, 0.0)
 
 
 def fields(solid, d, v, g):
-    """What the library reads back: drho and u = v - g/2 in FP64."""
+    """What the library reads back: drho and u = v - g/2."""
     fl = solid == 0
-    u = np.stack([np.where(fl, v[a].astype(np.float64) - 0.5 * g[a], 0.0) for a in range(3)])
-    return d.astype(np.float64), u
+    return d, np.stack([np.where(fl, v[a] - 0.5 * g[a], 0.0) for a in range(3)])

@@ -1,7 +1,7 @@
-"""Kernel 0 is the plain evaluation of the update, bit for bit, in every
-precision: FP64 mode is the reference of the others, and no operation of the
-FP32 modes is less than correctly rounded.  Sizes at the edges of the row
-kernel's windows and z-segments, and rows of a few nodes."""
+"""Kernel 0's arithmetic.  FP64, the reference of the other modes, is the plain
+evaluation of the update, bit for bit; no rounding of FP32 leans to one side.
+Sizes at the edges of the row kernel's windows and z-segments, and rows of a few
+nodes."""
 import numpy as np
 import pytest
 
@@ -22,32 +22,19 @@ def same(got, ref):
     return np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
 
 
-@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
 @pytest.mark.parametrize("q", [15, 19, 27])
-def test_bits_of_the_plain_step(q, prec):
+def test_fp64_bits_of_the_plain_step(q):
     for dims in DIMS:
         solid, drho, u = inputs.random_state(*dims, seed=sum(dims))
-        d, v = plain_step.start(solid, drho, u, G, prec)
-        print(f"[case] exact q={q} {prec} {dims}", flush=True)
-        sim, out = run_gpu([(solid, drho, u)], q, prec, G, 0, kernel=0)
+        d, v = plain_step.start(solid, drho, u, G)
+        print(f"[case] exact q={q} {dims}", flush=True)
+        sim, out = run_gpu([(solid, drho, u)], q, "f64", G, 0, kernel=0)
         for n in (1, 6):
             sim.step(n)
             for _ in range(n):
-                d, v = plain_step.step(q, solid, d, v, G, prec)
+                d, v = plain_step.step(q, solid, d, v, G)
             assert same(sim.moments(0), plain_step.fields(solid, d, v, G)), (dims, n)
         sim.close()
-
-
-def test_bits_after_many_steps():
-    """A rounding that leans to one side in every step would collect here."""
-    solid, drho, u = inputs.random_state(37, 11, 9, seed=4)
-    d, v = plain_step.start(solid, drho, u, G, "f32")
-    print("[case] exact f32, 500 steps", flush=True)
-    sim, _ = run_gpu([(solid, drho, u)], 19, "f32", G, 500, kernel=0)
-    for _ in range(500):
-        d, v = plain_step.step(19, solid, d, v, G, "f32")
-    assert same(sim.moments(0), plain_step.fields(solid, d, v, G))
-    sim.close()
 
 
 @pytest.mark.parametrize("q", [15, 19, 27])
@@ -60,3 +47,26 @@ def test_fp64_bits_of_the_oracle(q, dims):
     ref = oracle.run(q, oracle.State(*s), (0.0, 0.0, 0.0), 20)
     assert same(out[0], (ref.drho, ref.u))
     sim.close()
+
+
+@pytest.mark.parametrize("q", [15, 19, 27])
+@pytest.mark.parametrize("dims", [(150, 50, 40), (2, 400, 380)])
+def test_fp32_step_has_no_bias(q, dims):
+    """The regression of one step's error on the exact value.  The weights' unit
+    (1/72, 1/36, 1/216) is 7.45e-9 too large as a float: used as it is, density or
+    velocity has that slope in every step.  Roundings to nearest of a random state
+    scatter by about 2^-24 of the summed terms, a few times the value: over 3e5
+    nodes the slope of that scatter is below 1e-9, well within the bound of half the
+    unit's."""
+    solid, drho, u = inputs.random_state(*dims, seed=q)
+    g = (0.0, 0.0, 0.0)
+    print(f"[case] fp32 bias q={q} {dims}", flush=True)
+    sim, out = run_gpu([(solid, drho, u)], q, "f32", g, 0, kernel=0)
+    ref = oracle.run(q, oracle.State(solid, *out[0]), g, 1)   # from the state as stored
+    sim.step(1)
+    got = sim.moments(0)
+    sim.close()
+    for name, a, b in (("drho", got[0], ref.drho), ("u", got[1], ref.u)):
+        slope = np.sum((a - b) * b) / np.sum(b * b)
+        print(f"[err] fp32 bias q={q} {dims} {name}: {slope:.2e}", flush=True)
+        assert abs(slope) <= 0.5 * 7.45e-9, (name, slope)

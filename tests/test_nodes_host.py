@@ -20,7 +20,7 @@ def test_rows_of_a_few_nodes_do_not_take_a_wave_each(tmp_path):
             for q in (15, 19, 27):
                 for s in [(1, 300, 200), (2, 200, 100), (4, 150, 150), (8, 200, 200)]:
                     assert grid(p, q, s) == per_node(s), (p, q, s)
-                for s in [(1, 20, 30), (8, 20, 20), (20, 200, 200), (64, 60, 60), (150, 40, 30)]:
+                for s in [(1, 20, 30), (8, 20, 20), (24, 200, 200), (64, 60, 60), (150, 40, 30)]:
                     assert grid(p, q, s) != per_node(s), (p, q, s)
         many = [(1, 300, 200), (70, 9, 8)]
         assert grid("f64", 19, *many) == per_node(*many)
