@@ -135,7 +135,7 @@ typedef struct {
                                    tau1_permeability)                       */
     int32_t f16_log2_scale_u;   /* F16 scale of the stored velocity u + g/2,
                                    0 = 16; same range and check as above    */
-    const char *tune_cache; /* path of the autotune JSON cache, or NULL         */
+    const char *tune_cache; /* path of the autotune cache (text), or NULL       */
     int32_t layout;         /* state layout: -1 = automatic (packed for F32,
                                F16 and BF16 z-march contexts unless tile is
                                0-11, dense otherwise), 0 = dense, 1 = packed
@@ -188,7 +188,7 @@ typedef struct {
     int64_t work_items;      /* work items per step: z-march row groups x
                                 z-segments holding a fluid node, or waves of
                                 64 stored chunks for the chunk tile; 0 for
-                                the row kernel                              */
+                                kernels 0 and 2                             */
     int32_t launches_per_step; /* kernel launches one step takes (one per
                                 z-march lane layout, or one for all the
                                 one-chunk rows with batch_graph 3; 1 on D2Q9,

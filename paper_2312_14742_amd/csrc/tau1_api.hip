@@ -28,7 +28,7 @@ using namespace tau1;
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr int64_t kStageNodes = int64_t(1) << 21;   // upload/readback chunk
+constexpr int64_t kStageNodes = int64_t(1) << 21;   // nodes staged at a time
 constexpr int kMaxSamples = 1 << 16;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -45,9 +45,10 @@ struct SampleHost {
 // Byte layout of the workspace for one descriptor.
 struct Plan {
     size_t samples_off = 0;   // SampleDev[nsamples]
-    size_t partial_off = 0;   // reduction partials + result + counters
+    size_t partial_off = 0;   // reduction partials; results and the readback's flag
+                              // where there is no pinned memory
     size_t tiles_off = 0;     // z-march work list
-    size_t stage_off = 0;     // upload / readback staging
+    size_t stage_off = 0;     // staging: uploads, and readback without pinned memory
     size_t stage_bytes = 0;
     size_t total = 0;
     int64_t ntiles = 0;
@@ -323,7 +324,7 @@ Plan make_plan(const tau1_desc* d, bool tables) {
     }
     const int64_t stage_nodes = std::min<int64_t>(maxn, kStageNodes);
     p.stage_off = off;
-    // solid byte + drho + 3 u (FP64) on upload; 4 FP64 on readback
+    // solid byte + drho + 3 u (FP64) on upload; a staged readback takes the 4 FP64
     p.stage_bytes = align_up((size_t)stage_nodes * 40 + kAlign, kAlign);
     off += p.stage_bytes;
     p.total = off;
@@ -476,7 +477,7 @@ int group_resident(const tau1_ctx* ctx, const tau1_ctx::ZGroup& g) {
     return n;
 }
 
-// Launch geometry of one step kernel: z-march group g (kernel 1), the row
+// Launch geometry of one step kernel: z-march group g (kernel 1), the row or node
 // kernel over every sample (kernel 0) or the D2Q9 kernel (2).
 Launch step_launch(const tau1_ctx* ctx, int kernel, int tile, int g) {
     Launch l{};
@@ -592,7 +593,8 @@ void destroy_graph(tau1_ctx* ctx) {
 }
 
 // Graph of graph_chunk time steps.  The parity alternates step by step (D2Q9:
-// launch by launch) and, graph_chunk being even, the graph maps the current buffer onto itself.
+// launch by launch) and, graph_chunk being even, the graph maps the current
+// buffer onto itself.
 // A context with several launch groups (a batch of several z-march lane
 // layouts) either runs them as one chain -- the launches of a step one after
 // another, each with the whole GPU -- or as one chain per group, the chains
@@ -965,10 +967,10 @@ tau1_status reduce_ws(tau1_ctx* ctx, int s, int axis, double out[4]) {
     return st;
 }
 
-// Selects the tile of every lane layout (`tile`, or per_variant[v] where
-// that is given and not -1; kAutoTile: the automatic choice), rebuilds and uploads the work lists;
-// cached graphs are rebuilt on the next step.  The context's tile is that of
-// the layout with the most fluid nodes.  With `merge`, the one-row, one-chunk
+// Selects the tile of every lane layout (`tile`, or per_variant[v] where that is
+// given and not -1; kAutoTile: the automatic choice), rebuilds and uploads the
+// work lists; cached graphs are rebuilt on the next step.  The context's tile is
+// that of the layout with the most fluid nodes.  With `merge`, the one-row, one-chunk
 // layouts whose tiles run the shared-row schedule of one mode (that of the
 // layout with the most work among them) share one launch, k_zmarch_rows,
 // over their lists laid end to end; the other layouts launch alone.
@@ -1423,7 +1425,7 @@ tau1_status tau1_autotune(tau1_ctx* ctx, int32_t trial_steps) {
     tau1_status st = check_usable(ctx);
     if (st != TAU1_OK) return st;
     if (trial_steps < 1) return TAU1_E_INVALID;
-    if (!zmarch_eligible(ctx)) return TAU1_OK;  // only the row kernel applies
+    if (!zmarch_eligible(ctx)) return TAU1_OK;  // only kernel 0 applies
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));

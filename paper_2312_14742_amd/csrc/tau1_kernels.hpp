@@ -208,10 +208,14 @@ inline int64_t d2q9_blocks(SH* s, int n, int steps) {
 
 // Steps per launch for a context's samples: the number with the shortest
 // modelled time a step.  A launch takes 3.4 us alone and 5 us with a workgroup
-// on every CU, and 1.1-1.4 us a step for each round of them (fitted to 1-10
-// steps per launch; measured us a step at the choice and at one step per
-// launch: 40^2 nodes 1.4 / 4.6, 160^2 1.5 / 4.9, 400^2 3.1 / 6.4, 1000 x 100
-// 2.3 / 5.8, 1600 x 200 5.1 / 10.5).
+// on every CU, and 1.1-1.4 us a step for each round of them (fitted in FP64 to
+// 1-10 steps per launch; measured us a step at the choice and at one step per
+// launch: 40^2 nodes 1.4 / 4.6, 160^2 1.7 / 4.9, 400^2 3.1 / 6.4, 1000 x 100
+// 2.1 / 5.8, 1600 x 200 5.1 / 10.5).  FP32 steps are shorter and larger lattices
+// run two workgroups on a CU, which the model leaves out; against one thread per
+// node and one step per launch the choice still gives, FP64 / FP32, 1000^2 nodes
+// 25.7 -> 12.6 / 18.6 -> 7.2, 3000 x 1000 66 -> 50 / 48 -> 32, 6000^2 967 -> 638 /
+// 660 -> 362 us a step.
 template <typename SH>
 inline int d2q9_steps(SH* s, int n) {
     int best = 1;
