@@ -1157,9 +1157,22 @@ constexpr int zr_waves_per_simd(int q, int p, int v, int mode) {
     return g != 1 && (mode == 1 || mode == 3) ? 2 : 1;
 }
 
-// Work item (4 x int32): sample, row group, z-segment start, z-segment end.
-// Workgroups are remapped so that each XCD walks a contiguous range of items
-// (neighbouring rows share their y-1 / y+1 reads in that XCD's L2).  Each
+// Block of items of workgroup b of nwg (whole rounds of 8).  Dispatch is
+// round-robin over 8 XCDs; each XCD takes runs of kZrRun consecutive blocks, so
+// that neighbouring rows share their y-1 / y+1 reads in that XCD's L2, while the
+// XCDs advance through the list together: its parts may cost unequally (a batch
+// of several layouts and porosities: the 64-sample batch in one launch 82 GFLUPS
+// with one range per XCD, 94 with runs; as chains 107 and 109).  The last run is
+// shared out evenly.
+constexpr int kZrRun = 256;
+__device__ __forceinline__ int zr_block(int b, int nwg) {
+    constexpr int round = 8 * kZrRun;
+    const int first = b / round * round;
+    const int per = min(round, nwg - first) / 8, k = b - first;
+    return first + k % 8 * per + k / 8;
+}
+
+// Work item (4 x int32): sample, row group, z-segment start, z-segment end.  Each
 // instance compiles one lane layout V (its register budget alone sets the
 // occupancy); batches of differently sized samples launch one instance per
 // layout present.
@@ -1184,12 +1197,7 @@ void k_zmarch(StepArgs a) {
         for (int i = __lane_id(); i < 4 * kPX * 64; i += 64) lds_wave[i] = 0.0f;
         __builtin_amdgcn_wave_barrier();
     }
-    const int nwg = gridDim.x;
-    const int b = blockIdx.x;
-    // XCD-aware order: dispatch is round-robin over 8 XCDs
-    const int per = (nwg + 7) / 8;
-    const int xcd = b % 8, k = b / 8;
-    const int lb = xcd * per + k;
+    const int lb = zr_block(blockIdx.x, gridDim.x);
     // the item index is uniform across the wave; say so, so that every
     // per-item quantity (sample descriptor, buffer resources) stays scalar
     const int item = __builtin_amdgcn_readfirstlane(lb * kZrWaves + wave);
@@ -1251,11 +1259,7 @@ void k_zmarch_rows(StepArgs a) {
     constexpr int kLds = 2 * kZrWaves * kSlotComps * zr_rows_px() * 64;
     __shared__ float lds_all[kLds];
     const int wave = threadIdx.x >> 6;
-    const int nwg = gridDim.x;
-    const int b = blockIdx.x;
-    const int per = (nwg + 7) / 8;
-    const int xcd = b % 8, k = b / 8;
-    const int lb = xcd * per + k;
+    const int lb = zr_block(blockIdx.x, gridDim.x);
     const int item = __builtin_amdgcn_readfirstlane(lb * kZrWaves + wave);
     if (item >= a.ntiles) return;
     typedef int wi4 __attribute__((ext_vector_type(4)));
@@ -1338,7 +1342,7 @@ inline void* pick_zmarch_rows(int q, int p, int mode) {
 // One workgroup per four items, rounded to whole XCD rounds.  (With at most 2048
 // workgroups the rest of a longer list was a second item for the first of them,
 // which the XCD-aware order puts on the same XCDs: 512 x 300 x 511 at segments of
-// 16 planes, 2400 workgroups' worth, 730 us a step with the limit, 528 without.
+// 16 planes, 2400 workgroups' worth, 730 us a step with the limit, 487 without.
 // It also took a barrier between the two items.)
 inline int64_t zmarch_grid(int64_t nitems) {
     const int64_t wgs = (nitems + kZrWaves - 1) / kZrWaves;
