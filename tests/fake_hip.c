@@ -14,6 +14,7 @@ int fake_grid;                     /* workgroups of the last launch */
 int fake_launches, fake_graph_builds, fake_graph_nodes, fake_events, fake_pinned, fake_copies;
 int fake_freed_here, fake_freed;   /* hipHostFree: on the main thread, on any */
 int fake_refuse_pinned, fake_capturing;
+#define INC(c) __atomic_add_fetch(&(c), 1, __ATOMIC_SEQ_CST)   /* calls come from several threads */
 static pthread_t main_thread;
 
 __attribute__((constructor)) static void init(void) { main_thread = pthread_self(); }
@@ -29,20 +30,20 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, s
 int hipHostMalloc(void **p, size_t n, unsigned flags) {
     fake_pinned_flags = flags;
     if (fake_refuse_pinned) return OUT_OF_MEMORY;
-    ++fake_pinned;
+    INC(fake_pinned);
     *p = calloc(1, n);
     return OK;
 }
 int hipHostFree(void *p) {
-    if (pthread_equal(pthread_self(), main_thread)) ++fake_freed_here;
-    __atomic_add_fetch(&fake_freed, 1, __ATOMIC_SEQ_CST);
+    if (pthread_equal(pthread_self(), main_thread)) INC(fake_freed_here);
+    INC(fake_freed);
     free(p);
     return OK;
 }
 int hipEventCreate(void **e) { *e = malloc(1); return OK; }
 int hipEventCreateWithFlags(void **e, unsigned flags) {
     fake_event_flags = flags;
-    ++fake_events;
+    INC(fake_events);
     *e = malloc(1);
     return OK;
 }
@@ -55,7 +56,7 @@ int hipStreamIsCapturing(void *s, int *st) { (void)s; *st = fake_capturing; retu
 int hipThreadExchangeStreamCaptureMode(int *m) { *m = 0; return OK; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *st) {
     (void)kind; (void)st;
-    ++fake_copies;
+    INC(fake_copies);
     memcpy(d, s, n);
     return OK;
 }
@@ -74,20 +75,20 @@ int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *l, void **s) {
 int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **a, size_t l, void *s) {
     (void)f; (void)b; (void)a; (void)l; (void)s;
     fake_grid = (int)g.x;
-    ++fake_launches;
+    INC(fake_launches);
     return OK;
 }
 int hipGraphCreate(void **g, unsigned f) { (void)f; *g = malloc(1); return OK; }
 int hipGraphDestroy(void *g) { free(g); return OK; }
 int hipGraphAddKernelNode(void **n, void *g, const void *d, size_t k, const void *p) {
     (void)g; (void)d; (void)k; (void)p;
-    ++fake_graph_nodes;
+    INC(fake_graph_nodes);
     *n = (void *)(uintptr_t)fake_graph_nodes;
     return OK;
 }
 int hipGraphInstantiate(void **e, void *g, void *n, char *l, size_t s) {
     (void)g; (void)n; (void)l; (void)s;
-    ++fake_graph_builds;
+    INC(fake_graph_builds);
     *e = malloc(1);
     return OK;
 }
